@@ -139,8 +139,8 @@ typedef struct {
     double beta[2];       /* Heun: alpha = {0, 0.5}, beta = {1, 0.5} */
     int32_t slab;         /* tile depth of the stage kernel: 0 = default, 4 or 8 cells along z */
     int32_t scheme;       /* work split of the stage kernel: 0 = default (BMHD_SCHEME_BLOCK, or
-                             BMHD_SCHEME_PLANE when slab is 4, persist_wgs > 0 or the flux is
-                             BMHD_FLUX_LINDE); BMHD_SCHEME_FACE: one face per
+                             BMHD_SCHEME_PLANE when slab is 4 or persist_wgs > 0);
+                             BMHD_SCHEME_FACE: one face per
                              thread and direction, fluxes exchanged through LDS; BMHD_SCHEME_PLANE: one
                              wave per cell layer of the tile plus one wave for the tile's high-side faces,
                              fluxes exchanged across lanes (less LDS, more workgroups per CU);
@@ -382,7 +382,7 @@ int32_t bmhd_xchg_unpack(const bmhd_xchg *x, int32_t pass, int32_t r, const doub
  * own cells in the second stage) and written (d_Uout); dt is given per simulation (d_dt, the minimum over
  * every process: bmhd_reduce_dt stands in for that reduction on one GPU); positivity faults of the second
  * stage go to d_faults (may be NULL). Blocks clear of a body run on the block form, the others on the
- * plane form (all on the plane form with BMHD_FLUX_LINDE); the scheme, slab and graph options are not
+ * plane form; the scheme, slab and graph options are not
  * used. Faces on a level change record their fluxes for bmhd_xchg_flux_correct, which runs after every
  * process's stage (the fine side's records are in the one device's memory here; between GPUs they would
  * travel like the ghost messages). Errors: BMHD_EINVAL; BMHD_EUNSUPPORTED with a learned correction,

@@ -39,7 +39,7 @@ struct DevBlock {
     int32_t fc_skip;       // bit f: cells on face f are finished by the flux-correction kernel
     int32_t hb_pos[3];     // per direction d: index of the block's high face plane among those with no
                            // neighbour across them (learned correction's compact face layout), else -1
-    int32_t pad[2];
+    double inv_dx;         // 2^level / dx0
 };
 static_assert(sizeof(DevBlock) == 128, "DevBlock layout");
 

@@ -215,6 +215,7 @@ int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err) {
         B.sim = g.sim[b];
         B.level = g.level[b];
         for (int a = 0; a < 3; ++a) B.ijk[a] = g.ijk[3 * size_t(b) + a];
+        B.inv_dx = double(1 << B.level) / g.sdesc[B.sim].dx0;
         B.halo_slot = -1;
         for (int f = 0; f < 6; ++f) {
             B.fc_rec[f] = -1;

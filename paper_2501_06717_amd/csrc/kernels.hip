@@ -153,8 +153,88 @@ __device__ __forceinline__ void face_side(const R w[8], R U[8], R F[8], R &un, R
     cf = fast_speed<R, D, true>(w, ir);
 }
 
+// FP64 face flux. Every scheme is f = a F_L + b F_R + c (U_R - U_L) (HLLE: a = s_R / (s_R - s_L),
+// b = 1 - a, c = s_L a = -s_R b; Rusanov: a = b = 1/2, c = -c_max / 2), so the state differences fold into the
+// advected part of each side: with g_L = a u_nL - c and g_R = b u_nR + c, rho f = rho_L g_L + rho_R g_R and the
+// other components are multiply-add chains over rho g, g and the normal fields. The stage kernels are
+// bound by VALU issue: 141 slots per face this way against about 240 when both conserved states and both
+// physical fluxes are formed first and combined after.
+struct FaceSide {
+    double un, ub, pt, e, cf;
+};
+template <int D>
+__device__ __forceinline__ FaceSide face_side64(const double w[8]) {
+    constexpr int N = D, T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+    FaceSide s;
+    const double rho = w[0], p = w[7], bn = w[4 + N], b1 = w[4 + T1], b2 = w[4 + T2];
+    s.un = w[1 + N];
+    const double bt = fma(b2, b2, b1 * b1), bb = fma(bn, bn, bt);
+    const double uu = fma(w[1 + T2], w[1 + T2], fma(w[1 + T1], w[1 + T1], s.un * s.un));
+    s.ub = fma(w[1 + T2], b2, fma(w[1 + T1], b1, s.un * bn));
+    s.pt = fma(0.5, bb, p);
+    s.e = fma(0.5, rho * uu, fma(0.5, p, s.pt));
+    // fast speed: c_f^2 = x / rho with x = (gamma p + B^2 + sqrt((gamma p - B^2)^2 + 4 gamma p B_t^2)) / 2, so
+    // c_f = x / sqrt(x rho): two reciprocal square roots (one Newton step each) and no reciprocal of rho
+    const double gp = GAMMA * p, dd = gp - bb;
+    const double disc = fmax(fma(4.0 * gp, bt, dd * dd), 1e-300), rd = __builtin_amdgcn_rsq(disc), g = disc * rd;
+    const double x = 0.5 * (gp + bb + fma(g, fma(-g, 0.5 * rd, 0.5), g));
+    const double z = x * rho, r = __builtin_amdgcn_rsq(fmax(z, 1e-300));
+    const double xr = x * r;
+    s.cf = fma(0.5 * xr, fma(-(z * r), r, 1.0), xr);
+    return s;
+}
+
+template <int D, int FLUX>
+__device__ __forceinline__ void num_flux64(const double wl[8], const double wr[8], double f[8]) {
+    constexpr int N = D, T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+    const FaceSide L = face_side64<D>(wl), R = face_side64<D>(wr);
+    double a, b, c, sl = 0.0, sr = 0.0, inv = 0.0;
+    if constexpr (FLUX == BMHD_FLUX_RUSANOV) {
+        a = b = 0.5;
+        c = -0.5 * fmax(fabs(L.un) + L.cf, fabs(R.un) + R.cf);
+    } else {
+        // with sl = min(s_L, 0) and sr = max(s_R, 0) the single formula covers the three cases
+        sl = fmin(fmin(L.un - L.cf, R.un - R.cf), 0.0);
+        sr = fmax(fmax(L.un + L.cf, R.un + R.cf), 0.0);
+        inv = frcp1(sr - sl);
+        a = sr * inv;
+        b = -sl * inv;
+        c = sl * a;
+    }
+    const double al = a * L.un, br = b * R.un, gl = al - c, gr = br + c;
+    const double ml = wl[0] * gl, mr = wr[0] * gr, ql = a * wl[4 + N], qr = b * wr[4 + N];
+    f[0] = ml + mr;
+    f[1 + N] = fma(a, L.pt, fma(b, R.pt, fma(ml, L.un, fma(mr, R.un, fma(-ql, wl[4 + N], -qr * wr[4 + N])))));
+    f[1 + T1] = fma(ml, wl[1 + T1], fma(mr, wr[1 + T1], fma(-ql, wl[4 + T1], -qr * wr[4 + T1])));
+    f[1 + T2] = fma(ml, wl[1 + T2], fma(mr, wr[1 + T2], fma(-ql, wl[4 + T2], -qr * wr[4 + T2])));
+    f[4 + N] = c * (wr[4 + N] - wl[4 + N]);
+    f[4 + T1] = fma(gl, wl[4 + T1], fma(gr, wr[4 + T1], fma(-ql, wl[1 + T1], -qr * wr[1 + T1])));
+    f[4 + T2] = fma(gl, wl[4 + T2], fma(gr, wr[4 + T2], fma(-ql, wl[1 + T2], -qr * wr[1 + T2])));
+    f[7] = fma(gl, L.e, fma(gr, R.e, fma(al, L.pt, fma(br, R.pt, fma(-ql, L.ub, -qr * R.ub)))));
+    if constexpr (FLUX == BMHD_FLUX_LINDE) {
+        // Linde-type flux: the entropy wave's density jump (the part no pressure change explains, bounded by
+        // the jump) carried at the mean velocity and upwinded at the contact speed
+        const double drho = wr[0] - wl[0], dp = wr[7] - wl[7];
+        const double c2 = GAMMA * (wl[7] + wr[7]) * frcp1(wl[0] + wr[0]);
+        const double t = drho - dp * frcp1(c2);
+        const double delta = fmax(fmin(fmax(t, drho), 0.0), fmin(t, drho));
+        const double u0 = 0.5 * (wl[1] + wr[1]), u1 = 0.5 * (wl[2] + wr[2]), u2 = 0.5 * (wl[3] + wr[3]);
+        const double lam = fmin(fmax(N == 0 ? u0 : (N == 1 ? u1 : u2), sl), sr);
+        const double k = (sl * fmax(lam, 0.0) + sr * fmin(lam, 0.0) - sl * sr) * inv * delta;
+        f[0] += k;
+        f[1] = fma(k, u0, f[1]);
+        f[2] = fma(k, u1, f[2]);
+        f[3] = fma(k, u2, f[3]);
+        f[7] = fma(k, 0.5 * (u0 * u0 + u1 * u1 + u2 * u2), f[7]);
+    }
+}
+
 template <typename R, int D, int FLUX>
 __device__ __forceinline__ void num_flux(const R wl[8], const R wr[8], R f[8]) {
+    if constexpr (sizeof(R) == 8) {
+        num_flux64<D, FLUX>(wl, wr, f);
+        return;
+    } else {
     // Linde-type flux: the entropy wave's density jump (the part no pressure change explains, bounded by
     // the jump) and the mean velocity, formed before the face states' fluxes so that only these four
     // values stay live through them
@@ -194,17 +274,23 @@ __device__ __forceinline__ void num_flux(const R wl[8], const R wr[8], R f[8]) {
             f[7] += k * (R(0.5) * (ub[0] * ub[0] + ub[1] * ub[1] + ub[2] * ub[2]));
         }
     }
+    }
 }
 
 // Half of the monotonized-central limited slope, minmod(2 dm, (dm + dp) / 2, 2 dp) / 2, from the two
-// one-sided differences. With s = sign(dm + dp) it is s * max(0, min(|dm + dp| / 4, s dm, s dp)): the
-// same value bit for bit (every scaling is by a power of two), without branches.
-template <typename R>
-__device__ __forceinline__ R mc_half(R dm, R dp) {
-    const R c = dm + dp;
-    const R s = copysign(R(1), c);
-    const R q = rmax(R(0), rmin(rmin(R(0.25) * fabs(c), s * dm), s * dp));
-    return s * q;
+// one-sided differences: (dm + dp) / 4 clamped to the range between 0 and minmod(dm, dp). Every form below
+// gives the same value bit for bit (scalings by powers of two, comparisons). FP32: two v_med3; FP64 has no
+// median instruction, and six min / max cost less than the sign products (v_mul_f64 twice, a copied sign and
+// its constant, two min, max, the product with the sign).
+__device__ __forceinline__ double mc_half(double dm, double dp) {
+    double quarter = 0.25;
+    asm("" : "+s"(quarter));  // a product: as a power of two it would become v_ldexp_f64 and a canonicalising max
+    const double c = quarter * (dm + dp);
+    const double hi = fmax(fmin(dm, dp), 0.0), lo = fmin(fmax(dm, dp), 0.0);
+    return fmax(lo, fmin(hi, c));
+}
+__device__ __forceinline__ float mc_half(float dm, float dp) {
+    return __builtin_amdgcn_fmed3f(0.25f * (dm + dp), __builtin_amdgcn_fmed3f(dm, dp, 0.0f), 0.0f);
 }
 
 // body membership of a cell from its centre (no contraction: must agree bit for bit everywhere)
@@ -489,6 +575,18 @@ __device__ __forceinline__ double cell_bound(const double w[8], double inv_dx) {
     const double ir = frcp(w[0]);
     const double cx = fast_speed<double, 0>(w, ir), cy = fast_speed<double, 1>(w, ir), cz = fast_speed<double, 2>(w, ir);
     return (fabs(w[1]) + cx) * inv_dx + (fabs(w[2]) + cy) * inv_dx + (fabs(w[3]) + cz) * inv_dx;
+}
+
+// For positive density and pressure: not below cell_bound, without its square roots per axis (no fast speed exceeds
+// sqrt(a^2 + B^2 / rho); the margin covers the rounding of both). NaN or infinite where the field is.
+__device__ __forceinline__ double bound_limit(const double w[8], double inv_dx) {
+    const double s = (GAMMA * w[7] + w[4] * w[4] + w[5] * w[5] + w[6] * w[6]) * frcp1(w[0]);
+    return (fabs(w[1]) + fabs(w[2]) + fabs(w[3]) + 3.0 * fsqrt1(s)) * inv_dx * (1.0 + 1e-10);
+}
+
+// The bound published so far (a cell whose bound_limit does not exceed it cannot change the maximum).
+__device__ __forceinline__ double running_max(const unsigned long long *slot) {
+    return __longlong_as_double((long long)__atomic_load_n(slot, __ATOMIC_RELAXED));
 }
 
 __device__ __forceinline__ double wave_max(double x) {
@@ -975,14 +1073,16 @@ __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A,
     const int tid = lane_tid();
     const bool owner = tid < SL::NCELLS;
     const bool body = owner && near_body && sM(tid);
-    const int cell = tid + slab * 64 * KS;
-    const size_t off = size_t(b) * 512 + cell;
+    // uniform base of the slab and a 32-bit lane offset (a register pair per variable instead of 64-bit lane
+    // addresses)
+    const size_t off0 = size_t(b) * 512 + slab * 64 * KS;
+    const unsigned at = unsigned(tid);
     double out[8];
     if (owner) {
         if (body) {
 #pragma unroll
             for (int v = 0; v < 8; ++v) out[v] = uin[v];
-            if (A.local_dt && A.write_dt) A.dt[off] = 0.0;
+            if (A.local_dt && A.write_dt) (A.dt + off0)[at] = 0.0;
         } else {
             if (POWELL) {
                 const double ux = double(sW[1][tid]), uy = double(sW[2][tid]), uz = double(sW[3][tid]);
@@ -1005,16 +1105,16 @@ __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A,
                 double w[8];
                 cons_to_prim(uin, w);
                 dtc = A.cfl * (1.0 / cell_bound(w, inv_dx));
-                A.dt[off] = dtc;
+                (A.dt + off0)[at] = dtc;
             } else {
-                dtc = A.dt[off];
+                dtc = (A.dt + off0)[at];
             }
             const double bdt = A.beta * dtc;
             if (A.use_u0) {
                 const double a0 = A.alpha, a1 = 1.0 - A.alpha;
 #pragma unroll
                 for (int v = 0; v < 8; ++v)
-                    out[v] = a0 * __builtin_nontemporal_load(A.U0 + v * vs + off) + a1 * uin[v] + bdt * rhs[v];
+                    out[v] = a0 * __builtin_nontemporal_load(&(A.U0 + v * vs + off0)[at]) + a1 * uin[v] + bdt * rhs[v];
             } else {
 #pragma unroll
                 for (int v = 0; v < 8; ++v) out[v] = uin[v] + bdt * rhs[v];
@@ -1023,7 +1123,7 @@ __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A,
 #pragma unroll
         // the stage result and U^n are streamed (stored / read once per stage): non-temporal, so that they
         // do not push the neighbours' halo cells out of L2
-        for (int v = 0; v < 8; ++v) __builtin_nontemporal_store(out[v], A.Uout + v * vs + off);
+        for (int v = 0; v < 8; ++v) __builtin_nontemporal_store(out[v], &(A.Uout + v * vs + off0)[at]);
         if constexpr (LEARN) {
             // reject the provisional state if it is not positive or leaves the widened range of the old
             // 7-point neighbourhood in density or pressure
@@ -1040,7 +1140,7 @@ __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A,
                 }
                 bad = learned_rejects(w[0], w[7], nr, A.tau, A.floor_rel);
             }
-            A.lrn_flags[off] = bad ? 1 : 0;
+            (A.lrn_flags + off0)[at] = bad ? 1 : 0;
         }
     }
 
@@ -1078,7 +1178,7 @@ __device__ __forceinline__ void slab_compute(const Tables &T, const StageArgs &A
     const bool owner = tid < SL::NCELLS;
 
     // three flux sweeps, one face per thread; fluxes meet their two cells through LDS
-    const double inv_dx = double(1 << B.level) / S.dx0;
+    const double inv_dx = B.inv_dx;
     double rhs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     double divb = 0.0;
     if (near_body) sweep<KS, R, 0, FLUX, true>(T, A, B, b, slab, sW, sM, sF);
@@ -1220,7 +1320,7 @@ __device__ __forceinline__ void wp_compute(const Tables &T, const StageArgs &A, 
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = tid & 63, ci = l & 7, cj = l >> 3;
     const bool cellw = w < KS;
-    const double inv_dx = double(1 << B.level) / S.dx0;
+    const double inv_dx = B.inv_dx;
     double rhs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     double divb = 0.0;
     R fl[8], fr[8], bb, bbr;
@@ -1308,9 +1408,9 @@ __device__ __forceinline__ void wp_compute(const Tables &T, const StageArgs &A, 
         for (int v = 0; v < 8; ++v) rhs[v] += (double(fl[v]) - double(fr[v])) * inv_dx;
         divb += (double(bbr) - double(bb)) * inv_dx;
         // the cell's own stage input, read again here rather than held in registers through the sweeps
-        const size_t vs = size_t(T.nb) * 512, off = size_t(b) * 512 + slab * 64 * KS + tid;
+        const size_t vs = size_t(T.nb) * 512, off0 = size_t(b) * 512 + slab * 64 * KS;
 #pragma unroll
-        for (int v = 0; v < 8; ++v) uin[v] = A.Uin[v * vs + off];
+        for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[unsigned(tid)];
     }
     cell_update<KS, R, POWELL, LEARN>(T, A, b, slab, uin, sW, mk, rhs, divb, inv_dx, red, redi, rng);
 }
@@ -1388,23 +1488,85 @@ __global__ void __launch_bounds__(64 * (KS + 1), (wp_waves_per_simd<KS, R>())) k
 // fluxes travel through the x/y halo space and the top halo layer once those are dead, and the
 // end-of-step reduction reuses the bottom halo layers, so two workgroups (sixteen wavefronts) share a
 // CU (the plane form on 8x8x4 slabs: ten). Blocks near a body run on the plane form in a second launch.
+// It is bound by VALU issue (80 % of the cycles): what counts is instructions. Sources that are uniform over a
+// wavefront (one face's halo per load), LDS indices by selects instead of the general slab numbering's
+// branches, the flux of num_flux64 and the limiter of mc_half took it from 2,126 to 1,718 instructions per
+// wavefront and the 256^3 wind's step from 2.55 to 2.2 ms (FP32 fluxes: 1.78 to 1.58 ms).
 
 constexpr int BLK_NT = 512;
 
-// Convert the gathered conserved values of a block and its face halos to primitives in LDS.
-template <typename R>
-__device__ __forceinline__ void gather_store_blk(const double (&u)[gather_npt<8, BLK_NT>()][8], R (*sW)[Slab<8>::NC]) {
-    const int tid = lane_tid();
-#pragma unroll
-    for (int m = 0; m < gather_npt<8, BLK_NT>(); ++m) {
-        // 1,280 cells over 512 threads: a wavefront's cells are all valid or all past the end
-        const int c = tid + m * BLK_NT;
-        if (c >= Slab<8>::NC) break;
-        double w[8];
-        cons_to_prim(u[m], w);
-#pragma unroll
-        for (int v = 0; v < 8; ++v) sW[v][c] = R(w[v]);
+// Conserved values of the halo cells of face fd of block b that a wavefront gathers, (x, y, z) block-local with
+// one coordinate outside the block: in place from the neighbour's interior, the boundary rule, the halo buffer
+// of a level change, or (VIEW) the process's padded view. fd and so the source are uniform over the wavefront:
+// scalar branches and bases, one 32-bit offset per lane.
+template <bool VIEW>
+__device__ __forceinline__ void load_halo(const Tables &T, const StageArgs &A, const DevBlock &B, int b, int fd, int x,
+                                          int y, int z, double (&u)[8]) {
+    const int rel = B.face[fd];
+    const double *p;
+    size_t stride = size_t(T.nb) * 512;
+    unsigned at;
+    if (VIEW && ((A.view_faces[b] >> fd) & 1)) {
+        p = A.view + size_t(A.view_local[b]) * 1728;
+        at = unsigned(((z + 2) * 12 + (y + 2)) * 12 + (x + 2));
+        stride = size_t(A.view_vs);
+    } else if (rel >= 0) {
+        p = A.Uin + size_t(rel) * 512;
+        at = unsigned(((z & 7) * 8 + (y & 7)) * 8 + (x & 7));
+    } else if (rel == FACE_OUTFLOW) {
+        p = A.Uin + size_t(b) * 512;
+        at = unsigned((min(max(z, 0), 7) * 8 + min(max(y, 0), 7)) * 8 + min(max(x, 0), 7));
+    } else if (rel == FACE_INFLOW) {
+        p = T.sims[B.sim].inflow_U;
+        at = 0;
+        stride = 1;
+    } else {
+        const int a = fd >> 1, along = a == 0 ? x : (a == 1 ? y : z);
+        const int layer = along < 0 ? -1 - along : along - 8;
+        const int t1 = a == 0 ? y : x, t2 = a == 2 ? y : z;
+        p = T.halo + size_t(B.halo_slot) * HALO_SLOT + size_t(fd) * HALO_FACE;
+        at = unsigned(layer * 64 + t2 * 8 + t1);
+        stride = 128;
     }
+#pragma unroll
+    for (int v = 0; v < 8; ++v) u[v] = (p + v * stride)[at];
+}
+
+// The block and its face halos as primitives in LDS: wavefront w loads cell layer w, then (w < 4) layer w of
+// z = -2, -1, 8, 9 and a quarter of the y halos or (w >= 4) a quarter of the x halos, each from one face.
+template <typename R, bool VIEW>
+__device__ __forceinline__ void gather_blk(const Tables &T, const StageArgs &A, const DevBlock &B, int b,
+                                           R (*sW)[Slab<8>::NC]) {
+    using SL = Slab<8>;
+    const size_t vs = size_t(T.nb) * 512;
+    const int tid = lane_tid();
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    double u0[8], u1[8], u2[8];
+    const double *own = A.Uin + size_t(b) * 512;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) u0[v] = (own + v * vs)[unsigned(tid)];
+    const int k = ((w & 1) << 2) + (l >> 4), side = (w >> 1) & 1;
+    int c1, c2 = 0;
+    if (w < 4) {
+        load_halo<VIEW>(T, A, B, b, 4 + side, l & 7, l >> 3, side ? 6 + w : w - 2, u1);
+        c1 = SL::ZLO + tid;
+        const int t = (l >> 3) & 1;
+        load_halo<VIEW>(T, A, B, b, 2 + side, l & 7, side ? 8 + t : t - 2, k, u2);
+        c2 = SL::YH + (k * 4 + 2 * side + t) * 8 + (l & 7);
+    } else {
+        const int t = l & 1, j = (l >> 1) & 7;
+        load_halo<VIEW>(T, A, B, b, side, side ? 8 + t : t - 2, j, k, u1);
+        c1 = SL::XH + (k * 8 + j) * 4 + 2 * side + t;
+    }
+    auto store = [&](const double (&u)[8], int c) {
+        double p[8];
+        cons_to_prim(u, p);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) sW[v][c] = R(p[v]);
+    };
+    store(u0, tid);
+    store(u1, c1);
+    if (w < 4) store(u2, c2);
 }
 
 // Rotate the vector components of a state into the frame of normal direction d (normal first, then the
@@ -1420,20 +1582,12 @@ __device__ __forceinline__ void rotate_in(int d, R w[8]) {
     }
 }
 
-// Flux through a face whose direction d (0, 1, 2) is chosen per lane, away from any body cell: the face
-// between the cells (i, j, k) - e_d and (i, j, k), block-local. The face states are reconstructed component
-// by component (the limiter acts on each component alone) and then rotated into the face-normal frame, so
-// one x-normal evaluation serves every direction; fr is the flux in that frame, bbar the face-averaged
-// normal field.
-template <typename R, int FLUX>
-__device__ __forceinline__ void face_flux_any(R (*sW)[Slab<8>::NC], int d, int i, int j, int k, R fr[8], R &bbar) {
-    using SL = Slab<8>;
-    int c[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int o = q - 2;
-        c[q] = SL::idx(i + (d == 0 ? o : 0), j + (d == 1 ? o : 0), k + (d == 2 ? o : 0));
-    }
+// Flux of direction D through the face between the cells at LDS indices c[1] and c[2], away from any body cell,
+// and the face-averaged normal field. With ROT the face is in the frame of direction d, chosen per lane: the
+// face states are reconstructed component by component (the limiter acts on each component alone) and then
+// rotated, so one x-normal evaluation serves every direction, and the flux comes out in that frame.
+template <typename R, int D, int FLUX, bool ROT = false>
+__device__ __forceinline__ void blk_face(R (*sW)[Slab<8>::NC], const int (&c)[4], R (&f)[8], R &bbar, int d = 0) {
     R wl[8], wr[8];
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
@@ -1442,13 +1596,15 @@ __device__ __forceinline__ void face_flux_any(R (*sW)[Slab<8>::NC], int d, int i
         wl[v] = b + mc_half(d0, d1);
         wr[v] = cc - mc_half(d1, d2);
     }
-    rotate_in(d, wl);
-    rotate_in(d, wr);
-    num_flux<R, 0, FLUX>(wl, wr, fr);
-    bbar = R(0.5) * (wl[4] + wr[4]);
+    if constexpr (ROT) {
+        rotate_in(d, wl);
+        rotate_in(d, wr);
+    }
+    num_flux<R, D, FLUX>(wl, wr, f);
+    bbar = R(0.5) * (wl[4 + D] + wr[4 + D]);
 }
 
-// Flux of a face of direction D from the rotated frame of face_flux_any back to x, y, z.
+// Flux of a face of direction D from the rotated frame of blk_face back to x, y, z.
 template <int D, typename R>
 __device__ __forceinline__ void unrotate(const R fr[8], R f[8]) {
     f[0] = fr[0];
@@ -1480,21 +1636,23 @@ __device__ __forceinline__ float lane_read(float x, int l) {
 
 // The four face passes, the source and the update of one block whose primitives are in LDS.
 template <typename R, int FLUX, bool POWELL>
-__device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A, int b, R (*sW)[Slab<8>::NC]) {
+__device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A, const DevBlock &B, int b,
+                                            R (*sW)[Slab<8>::NC], double inv_dx, bool fc) {
     using SL = Slab<8>;
-    const DevBlock &B = T.blocks[b];
-    const DevSim &S = T.sims[B.sim];
-    const BitMask mk{nullptr};  // no body cells in these blocks: never read
     const int tid = lane_tid();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = tid & 63, ci = l & 7, cj = l >> 3;
-    const double inv_dx = double(1 << B.level) / S.dx0;
     double rhs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     double divb = 0.0;
     R f[8], bb;
 
     // x: the low-x face of each cell; its flux enters the cell and, from the next lane, the cell below
-    face_flux<8, R, 0, FLUX, false, false>(T, A, B, b, 0, sW, mk, ci, cj, w, f, bb);
+    {
+        const int h = SL::XH + (w * 8 + cj) * 4;
+        const int c[4] = {ci < 2 ? h + ci : tid - 2, ci < 1 ? h + 1 : tid - 1, tid, ci > 6 ? h + 2 : tid + 1};
+        blk_face<R, 0, FLUX>(sW, c, f, bb);
+        if (fc) record_fc<0>(T, B, ci, cj, w, f);
+    }
     // the next lane's flux enters with weight inv_dx, or 0 in the last column (its high face comes later)
     const double wx = ci < 7 ? inv_dx : 0.0, wy = cj < 7 ? inv_dx : 0.0;
 #pragma unroll
@@ -1510,7 +1668,12 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     }
 
     // y: the low-y face of each cell; the cell below is eight lanes on
-    face_flux<8, R, 1, FLUX, false, false>(T, A, B, b, 0, sW, mk, ci, cj, w, f, bb);
+    {
+        const int h = SL::YH + w * 32 + ci;
+        const int c[4] = {cj < 2 ? h + cj * 8 : tid - 16, cj < 1 ? h + 8 : tid - 8, tid, cj > 6 ? h + 16 : tid + 8};
+        blk_face<R, 1, FLUX>(sW, c, f, bb);
+        if (fc) record_fc<1>(T, B, ci, cj, w, f);
+    }
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
         const R g = __shfl_down(f[v], 8, 64);
@@ -1528,12 +1691,26 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     // layer); the other lanes repeat face x = 8 of row 0
     R zf[8], zb;
     {
-        int d = 0, fi = 8, fj = 0, fk = w;
-        if (ci == 7) { fj = cj; }
-        else if (cj == 7 || l == 54) { d = 1; fi = cj == 7 ? ci : 7; fj = 8; }
-        else if (l < 7 || l == 8) { d = 2; fi = l == 8 ? 7 : l; fj = w; fk = 8; }
+        int d = 0, in = w * 64 + 6, st = 1, out = SL::XH + w * 32 + 2, so = 1, fi = 0;
+        if (ci == 7) {
+            in += cj * 8;
+            out += cj * 4;
+        } else if (cj == 7 || l == 54) {
+            d = 1;
+            fi = cj == 7 ? ci : 7;
+            in = w * 64 + 48 + fi;
+            st = so = 8;
+            out = SL::YH + w * 32 + 16 + fi;
+        } else if (l < 7 || l == 8) {
+            d = 2;
+            fi = l == 8 ? 7 : l;
+            in = 6 * 64 + w * 8 + fi;
+            st = so = 64;
+            out = SL::ZHI + w * 8 + fi;
+        }
+        const int c[4] = {in, in + st, out, out + so};
         R fr[8], bf;  // the flux in the face-normal frame
-        face_flux_any<R, FLUX>(sW, d, fi, fj, fk, fr, bf);
+        blk_face<R, 0, FLUX, true>(sW, c, fr, bf, d);
         // the y = 8 face of column 7 moves from lane 54 to lane 63
         R yr[8], yb;
 #pragma unroll
@@ -1545,7 +1722,7 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
 #pragma unroll
             for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(fx[v]), inv_dx, rhs[v]);
             divb = fma(double(bf), inv_dx, divb);
-            if (B.flags & BF_FC) record_fc<0>(T, B, 8, cj, w, fx);
+            if (fc) record_fc<0>(T, B, 8, cj, w, fx);
         }
         if (cj == 7) {
             R fy[8];
@@ -1555,12 +1732,12 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
 #pragma unroll
             for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(fy[v]), inv_dx, rhs[v]);
             divb = fma(double(by), inv_dx, divb);
-            if (B.flags & BF_FC) record_fc<1>(T, B, ci, 8, w, fy);
+            if (fc) record_fc<1>(T, B, ci, 8, w, fy);
         }
         if (l < 7 || l == 8) {
             unrotate<2>(fr, zf);
             zb = bf;
-            if (B.flags & BF_FC) record_fc<2>(T, B, fi, w, 8, zf);
+            if (fc) record_fc<2>(T, B, fi, w, 8, zf);
         }
     }
     // past this barrier the x/y halos and the top halo layer (z = 9) are dead: the z fluxes of face layers
@@ -1573,7 +1750,13 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         for (int v = 0; v < 8; ++v) sW[v][SL::XH + q] = zf[v];
         zbar[7 * SL::NC + w * 8 + (l == 8 ? 7 : l)] = zb;
     }
-    face_flux<8, R, 2, FLUX, false, false>(T, A, B, b, 0, sW, mk, ci, cj, w, f, bb);
+    {
+        // cell layers w - 2 .. w + 1, uniform over the wavefront (below the block: ZLO; above: ZHI = 8 layers on)
+        const int c[4] = {(w < 2 ? SL::ZLO + w * 64 : (w - 2) * 64) + l, (w < 1 ? SL::ZLO + 64 : (w - 1) * 64) + l, tid,
+                          (w > 6 ? SL::ZHI : (w + 1) * 64) + l};
+        blk_face<R, 2, FLUX>(sW, c, f, bb);
+        if (fc) record_fc<2>(T, B, ci, cj, w, f);
+    }
 #pragma unroll
     for (int v = 0; v < 8; ++v) rhs[v] = fma(double(f[v]), inv_dx, rhs[v]);
     divb = fma(-double(bb), inv_dx, divb);
@@ -1582,20 +1765,89 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         for (int v = 0; v < 8; ++v) sW[v][SL::XH + (w - 1) * 64 + l] = f[v];
         zbar[(w - 1) * SL::NC + l] = bb;
     }
-    __syncthreads();
-    double uin[8];
-    {
+    auto top_in = [&]() {  // the flux and normal field of each cell's high z face
 #pragma unroll
         for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(sW[v][SL::XH + w * 64 + l]), inv_dx, rhs[v]);
         divb = fma(double(zbar[w * SL::NC + l]), inv_dx, divb);
-        const size_t vs = size_t(T.nb) * 512, off = size_t(b) * 512 + tid;
-#pragma unroll
-        for (int v = 0; v < 8; ++v) uin[v] = A.Uin[v * vs + off];
-    }
-    // the bottom halo layers are dead here: the end-of-step reduction uses them
+    };
+    // the bottom halo layers are dead past the next barrier: the end-of-step reduction uses them
     double *red = reinterpret_cast<double *>(&sW[0][SL::ZLO]);
     int *redi = reinterpret_cast<int *>(&sW[1][SL::ZLO]);
-    cell_update<8, R, POWELL, false, BitMask, BLK_NT>(T, A, b, 0, uin, sW, mk, rhs, divb, inv_dx, red, redi);
+    const size_t vs = size_t(T.nb) * 512, off0 = size_t(b) * 512;
+    if constexpr (sizeof(R) == 4) {
+        // sized for 80 registers: everything is loaded where it is used (with the FP64 form's early loads a few
+        // values spill, and the wind on 256^3 takes 7.0-8.5 instead of 6.9 ms for four steps)
+        __syncthreads();
+        top_in();
+        double uin[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[unsigned(tid)];
+        cell_update<8, R, POWELL, false, BitMask, BLK_NT>(T, A, b, 0, uin, sW, BitMask{nullptr}, rhs, divb, inv_dx, red, redi);
+        return;
+    }
+    const int sim = B.sim, skipm = B.fc_skip;
+    // the cell's stage input, U^n, step and the running bound are on their way while the barrier waits. The stage
+    // result and U^n are streamed (stored / read once per stage): non-temporal, so that they do not push the
+    // neighbours' halo cells out of L2
+    const unsigned at = unsigned(tid);
+    double uin[8], u0[8], dtc = 0.0;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[at];
+    if (A.use_u0) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) u0[v] = __builtin_nontemporal_load(&(A.U0 + v * vs + off0)[at]);
+    }
+    if (!A.local_dt) dtc = A.dt[sim];
+    else if (!A.write_dt) dtc = (A.dt + off0)[at];
+    const double top = A.want_lam ? running_max(T.lam + sim) : 0.0;
+    __syncthreads();
+    top_in();
+    if (POWELL) {
+        const double ux = double(sW[1][tid]), uy = double(sW[2][tid]), uz = double(sW[3][tid]);
+        const double bx = double(sW[4][tid]), by = double(sW[5][tid]), bz = double(sW[6][tid]);
+        rhs[1] -= divb * bx;
+        rhs[2] -= divb * by;
+        rhs[3] -= divb * bz;
+        rhs[4] -= divb * ux;
+        rhs[5] -= divb * uy;
+        rhs[6] -= divb * uz;
+        rhs[7] -= divb * (ux * bx + uy * by + uz * bz);
+    }
+    if (A.local_dt && A.write_dt) {
+        // local time stepping: the cell's own CFL step from its stage input (the step's starting state), the same
+        // expression as the global step of one cell
+        double p[8];
+        cons_to_prim(uin, p);
+        dtc = A.cfl * (1.0 / cell_bound(p, inv_dx));
+        (A.dt + off0)[at] = dtc;
+    }
+    const double bdt = A.beta * dtc;
+    double out[8];
+    if (A.use_u0) {
+        const double a0 = A.alpha, a1 = 1.0 - A.alpha;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) out[v] = a0 * u0[v] + a1 * uin[v] + bdt * rhs[v];
+    } else {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) out[v] = uin[v] + bdt * rhs[v];
+    }
+#pragma unroll
+    for (int v = 0; v < 8; ++v) __builtin_nontemporal_store(out[v], &(A.Uout + v * vs + off0)[at]);
+    if (A.count_faults || A.want_lam) {
+        // end of a step: positivity check and the next time-step bound
+        const bool later = skipm && (((skipm & 1) && ci == 0) || ((skipm & 2) && ci == 7) || ((skipm & 4) && cj == 0) ||
+                                     ((skipm & 8) && cj == 7) || ((skipm & 16) && w == 0) || ((skipm & 32) && w == 7));
+        double lam = 0.0;
+        int nf = 0;
+        if (!later) {
+            double p[8];
+            cons_to_prim(out, p);
+            nf = !(p[0] > 0.0) || !(p[7] > 0.0) || !(p[7] < INFINITY);
+            // (a cell that is not positive always gives its own bound: the limit holds for positive states)
+            if (A.want_lam && (nf || !(bound_limit(p, inv_dx) <= top))) lam = cell_bound(p, inv_dx);
+        }
+        block_publish<BLK_NT>(lam, A.count_faults ? nf : 0, red, redi, A.want_lam ? T.lam + sim : nullptr, A.faults);
+    }
 }
 
 // Wavefronts per SIMD the register allocation is sized for. FP64: four (126 VGPRs; the 80 KiB of LDS
@@ -1613,13 +1865,12 @@ __global__ void __launch_bounds__(BLK_NT, (blk_waves_per_simd<R>())) k_stage_blk
     __shared__ R sW[8][SL::NC];
     const int wg = blockIdx.x, xcd = wg & 7, slot = wg >> 3;
     const int b = sched_block(T, A, xcd_first(sched_count(T, A), xcd) + slot);
-    {
-        double u[gather_npt<8, BLK_NT>()][8];
-        gather_issue<8, BLK_NT, VIEW>(T, A, b, 0, u);
-        gather_store_blk<R>(u, sW);
-    }
+    const DevBlock &B = T.blocks[b];
+    const double inv_dx = B.inv_dx;
+    const bool fc = (B.flags & BF_FC) != 0;
+    gather_blk<R, VIEW>(T, A, B, b, sW);
     __syncthreads();
-    blk_compute<R, FLUX, POWELL>(T, A, b, sW);
+    blk_compute<R, FLUX, POWELL>(T, A, B, b, sW, inv_dx, fc);
 }
 
 // Flux-correction target of every face of a level-0 grid C from the same simulations refined everywhere
@@ -2137,13 +2388,12 @@ int32_t launch_stage_prec(const HostGrid &h, const StageArgs &a, int flux, bool 
 
 Shape pick_shape(const bmhd_opts &o) {
     Shape sh;
-    // measured on the 256^3 magnetosphere: the block form in both precisions (FP64: 1.25 / 1.40 ms per
-    // stage against 1.74 / 2.07 for the plane form on 8x8x4 slabs and 1.91 / 2.16 for the face form on
-    // full blocks; FP32 flux: 0.94 / 1.14 against 1.04 / 1.26). A persistent grid or a tile of four
-    // layers asks for the plane form, and so does the Linde-type flux (its block form does not fit 128
-    // registers: 4.46 against 3.98 ms per step on the same grid). With the face form, full blocks for FP64.
+    // the block form for every flux and precision (256^3 magnetosphere, HLLE, FP64: 2.2 ms per step against 3.8 for
+    // the plane form on 8x8x4 slabs and 4.1 for the face form on full blocks; fast wave on 1,875 blocks with the
+    // Linde-type flux: 0.21 against 0.30 ms). A persistent grid or a tile of four layers asks for the plane form.
+    // With the face form, full blocks for FP64.
     if (o.scheme == 0)
-        sh.scheme = (o.persist_wgs > 0 || o.slab == 4 || o.flux == BMHD_FLUX_LINDE) ? BMHD_SCHEME_PLANE : BMHD_SCHEME_BLOCK;
+        sh.scheme = (o.persist_wgs > 0 || o.slab == 4) ? BMHD_SCHEME_PLANE : BMHD_SCHEME_BLOCK;
     else sh.scheme = o.scheme;
     sh.ks = o.slab == 0 ? ((o.precision == BMHD_FP64 && sh.scheme == BMHD_SCHEME_FACE) || sh.scheme == BMHD_SCHEME_BLOCK
                                ? 8 : 4)
@@ -2215,27 +2465,20 @@ int32_t check_opts(const bmhd_opts &o) {
 
 // One stage for a subset of blocks whose ghost cells come from a padded view (one process after the
 // ghost exchange between processes): the block form for the subset's blocks clear of a body and the plane
-// form for the others (the plane form for all of them with the Linde-type flux, as in bmhd_advance). No
+// form for the others, as in bmhd_advance. No
 // level-change halos (the view holds every ghost cell), no flux correction (flux_correct_subset, once the
 // stage has run for every process) and no next-dt bound.
 template <typename R, int FLUX, bool POWELL>
 int32_t launch_view_stage(const HostGrid &h, const StageArgs &a, const ViewStage &v, hipStream_t s) {
     StageArgs ac = a, an = a;
-    if constexpr (FLUX == BMHD_FLUX_LINDE) {
-        an.sched = v.split;
-        an.n_sched = v.n_total;
-        if (v.n_total) k_stage_wp<4, R, FLUX, POWELL, false, false, true><<<v.n_total * 2, Slab<4>::NT, 0, s>>>(h.dev, an);
-        return launch_check("stage kernel");
-    } else {
-        const int nn = v.n_total - v.n_clear;
-        ac.sched = v.split;
-        ac.n_sched = v.n_clear;
-        an.sched = v.split + v.n_clear;
-        an.n_sched = nn;
-        if (nn) k_stage_wp<4, R, FLUX, POWELL, false, false, true><<<nn * 2, Slab<4>::NT, 0, s>>>(h.dev, an);
-        if (v.n_clear) k_stage_blk<R, FLUX, POWELL, true><<<v.n_clear, BLK_NT, 0, s>>>(h.dev, ac);
-        return launch_check("stage kernel");
-    }
+    const int nn = v.n_total - v.n_clear;
+    ac.sched = v.split;
+    ac.n_sched = v.n_clear;
+    an.sched = v.split + v.n_clear;
+    an.n_sched = nn;
+    if (nn) k_stage_wp<4, R, FLUX, POWELL, false, false, true><<<nn * 2, Slab<4>::NT, 0, s>>>(h.dev, an);
+    if (v.n_clear) k_stage_blk<R, FLUX, POWELL, true><<<v.n_clear, BLK_NT, 0, s>>>(h.dev, ac);
+    return launch_check("stage kernel");
 }
 
 template <typename R, int FLUX>
