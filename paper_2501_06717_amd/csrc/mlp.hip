@@ -369,6 +369,327 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const float *
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Training step on the matrix cores: the forward that keeps the pre-activations, and a backward pass in three
+// launches. A training batch is a few thousand samples (4,096: 0.9 GFLOP), so what counts is that every CU has
+// work and that few launches depend on one another; one product per launch over 32 x 32 tiles left all but 4-16
+// workgroups idle in the weight gradients (K = the samples, 165 us each) and took 22 launches: 1.43 ms for
+// loss, gradient and Adam at 4,096 samples of the 128-wide network, now 55 us (kernels 11, 14, 17 and 4.5 us).
+//   k_mlp_forward_save  one workgroup of four wavefronts per 16 samples, the output columns shared out over the
+//                       wavefronts, every weight fragment loaded up front;
+//   k_mlp_back_chain    the same split for dY -> dZ3 -> dZ2 -> dZ1, the dZ stored in BF16 and transposed (samples
+//                       contiguous, as the next products' operands), the bias gradients as sums per 16 samples;
+//   k_mlp_weight_grad   all four weight gradients, 32 x 32 blocks, the samples split over the eight wavefronts
+//                       of a workgroup and over `splits` workgroups; inputs silu(Z) formed on the fly;
+//   k_mlp_grad_sum      the sums over the splits and over the 16-sample tiles, in a fixed order.
+// Rounding points (BF16 operands, FP32 sums) are those of the product per launch; only the order of the sums
+// over samples differs.
+
+template <int H>
+__global__ void __launch_bounds__(256) k_mlp_forward_save(const float *__restrict__ P, const __bf16 *__restrict__ Pb,
+                                                          int n, const float *__restrict__ X, float *__restrict__ Y,
+                                                          float *__restrict__ Z) {
+    constexpr int NT = H / 16, NC = H / 32, TW = (NT + 3) / 4, LD = H + 8;
+    __shared__ __attribute__((aligned(16))) __bf16 act[2][16 * LD];
+    const MlpView V = mlp_view(H);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
+    const int s0 = blockIdx.x * 16;
+    bf16x8 w1[TW], w2[TW][NC], w3[TW][NC], w4[NC];
+    float b[3][TW], b4 = 0.0f;
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        const int o = min(wave + 4 * t, NT - 1) * 16 + r;
+        w1[t] = *reinterpret_cast<const bf16x8 *>(Pb + V.off_w[0] + long(o) * MLP_IN + 8 * q);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            w2[t][c] = *reinterpret_cast<const bf16x8 *>(Pb + V.off_w[1] + long(o) * H + 32 * c + 8 * q);
+            w3[t][c] = *reinterpret_cast<const bf16x8 *>(Pb + V.off_w[2] + long(o) * H + 32 * c + 8 * q);
+        }
+#pragma unroll
+        for (int l = 0; l < 3; ++l) b[l][t] = P[V.off_b[l] + o];
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (r < MLP_OUT) w4[c] = *reinterpret_cast<const bf16x8 *>(Pb + V.off_w[3] + long(r) * H + 32 * c + 8 * q);
+            else
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w4[c][j] = __bf16(0.0f);
+        }
+        b4 = r < MLP_OUT ? P[V.off_b[3] + r] : 0.0f;
+    }
+    for (int e = threadIdx.x; e < 16 * MLP_IN; e += 256) {
+        const int m = e / MLP_IN, k = e % MLP_IN;
+        act[0][m * LD + k] = __bf16(s0 + m < n ? X[size_t(s0 + m) * MLP_IN + k] : 0.0f);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const __bf16 *in = act[l & 1];
+        __bf16 *out = act[(l + 1) & 1];
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            if (wave + 4 * t >= NT) break;
+            f32x4 acc = {b[l][t], b[l][t], b[l][t], b[l][t]};
+            constexpr int nc0 = MLP_IN / 32;
+#pragma unroll
+            for (int c = 0; c < (l == 0 ? nc0 : NC); ++c) {
+                const bf16x8 av = *reinterpret_cast<const bf16x8 *>(in + r * LD + 32 * c + 8 * q);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, l == 0 ? w1[t] : (l == 1 ? w2[t][c] : w3[t][c]), acc, 0, 0, 0);
+            }
+            const int o = (wave + 4 * t) * 16 + r;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = 4 * q + i;
+                if (s0 + m < n) Z[(size_t(l) * n + s0 + m) * H + o] = acc[i];
+                out[m * LD + o] = __bf16(silu(acc[i]));
+            }
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+        f32x4 acc = {b4, b4, b4, b4};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const bf16x8 av = *reinterpret_cast<const bf16x8 *>(act[1] + r * LD + 32 * c + 8 * q);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w4[c], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int m = 4 * q + i;
+            if (r < MLP_OUT && s0 + m < n) Y[size_t(s0 + m) * MLP_OUT + r] = acc[i];
+        }
+    }
+}
+
+// Work area of the fused backward pass, in floats: dZ of the three hidden layers as [layer][H][npad] BF16, the
+// bias sums per 16 samples [npad / 16][3 H + 8], the weight gradients per split [splits][n_params].
+struct BackLayout {
+    long npad, dbias, part;
+    int splits;  // 1: the weight gradients go straight to the result; 0: the work area is too small
+};
+inline BackLayout back_layout(int H, int n, size_t work_floats) {
+    BackLayout b;
+    b.npad = (long(n) + 31) / 32 * 32;
+    b.dbias = 3 * long(H) * b.npad / 2;
+    b.part = b.dbias + b.npad / 16 * (3 * H + 8);
+    const long hb = H / 32, blocks = 2 * hb + 2 * hb * hb;
+    if (size_t(b.part) > work_floats) {
+        b.splits = 0;
+        return b;
+    }
+    // about 320 workgroups, four K steps of 32 samples or more for each
+    long s = (long(work_floats) - b.part) / mlp_params(H);
+    if (s > 320 / blocks) s = 320 / blocks;
+    if (s > b.npad / 128) s = b.npad / 128;
+    b.splits = s < 1 ? 1 : int(s);
+    return b;
+}
+
+template <int H>
+__global__ void __launch_bounds__(256) k_mlp_back_chain(const float *__restrict__ P, int n, long npad,
+                                                        const float *__restrict__ Tt, const float *__restrict__ Y,
+                                                        const float *__restrict__ Z, float *__restrict__ sqerr,
+                                                        __bf16 *__restrict__ dzt, float *__restrict__ dbias) {
+    constexpr int NT = H / 16, NC = H / 32, TW = (NT + 3) / 4, LD = H + 8;
+    __shared__ __attribute__((aligned(16))) __bf16 dz[2][16 * LD];
+    __shared__ float sdy[16][MLP_OUT];
+    const MlpView V = mlp_view(H);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
+    const int s0 = blockIdx.x * 16;
+    float *db = dbias + long(blockIdx.x) * (3 * H + 8);
+    // this wavefront's columns of W4, W3 and W2 as B operands: lane (q, r) rows 8q .. 8q + 7 of column r
+    bf16x8 w4[TW], w3[TW][NC], w2[TW][NC];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        const int i = min(wave + 4 * t, NT - 1) * 16 + r;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w4[t][j] = q == 0 ? __bf16(P[V.off_w[3] + long(j) * H + i]) : __bf16(0.0f);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                w3[t][c][j] = __bf16(P[V.off_w[2] + long(32 * c + 8 * q + j) * H + i]);
+                w2[t][c][j] = __bf16(P[V.off_w[1] + long(32 * c + 8 * q + j) * H + i]);
+            }
+    }
+    float z[3][TW][4];
+#pragma unroll
+    for (int l = 2; l >= 0; --l)
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                z[l][t][i] = s0 + 4 * q + i < n ? Z[(size_t(l) * n + s0 + 4 * q + i) * H + min(wave + 4 * t, NT - 1) * 16 + r] : 0.0f;
+    // dY = 2 (Y - T) / (8 n) and the squared errors
+    if (threadIdx.x < 16 * MLP_OUT) {
+        const int m = threadIdx.x / MLP_OUT, o = threadIdx.x % MLP_OUT;
+        float dy = 0.0f;
+        if (s0 + m < n) {
+            const size_t e = size_t(s0 + m) * MLP_OUT + o;
+            const float d = Y[e] - Tt[e];
+            dy = 2.0f * d / (8.0f * float(n));
+            sqerr[e] = d * d;
+        }
+        sdy[m][o] = dy;
+    }
+    __syncthreads();
+    if (threadIdx.x < MLP_OUT) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int m = 0; m < 16; ++m) sum += sdy[m][threadIdx.x];
+        db[3 * H + threadIdx.x] = sum;
+    }
+#pragma unroll
+    for (int l = 2; l >= 0; --l) {
+        const __bf16 *in = dz[(l + 1) & 1];
+        __bf16 *out = dz[l & 1];
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            if (wave + 4 * t >= NT) break;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            if (l == 2) {
+                bf16x8 av;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) av[j] = q == 0 ? __bf16(sdy[r][j]) : __bf16(0.0f);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w4[t], acc, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const bf16x8 av = *reinterpret_cast<const bf16x8 *>(in + r * LD + 32 * c + 8 * q);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, l == 1 ? w3[t][c] : w2[t][c], acc, 0, 0, 0);
+                }
+            }
+            const int o = (wave + 4 * t) * 16 + r;
+            float sum = 0.0f;
+            bf16x4 h;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = 4 * q + i;
+                float d = 0.0f;
+                if (s0 + m < n) d = acc[i] * silu_grad(z[l][t][i]);
+                sum += d;
+                h[i] = __bf16(d);
+                if (l > 0) out[m * LD + o] = h[i];
+            }
+            sum += __shfl_xor(sum, 16);
+            sum += __shfl_xor(sum, 32);
+            if (q == 0) db[l * H + o] = sum;
+            *reinterpret_cast<bf16x4 *>(dzt + (long(l) * H + o) * npad + s0 + 4 * q) = h;
+        }
+        if (l > 0) __syncthreads();
+    }
+}
+
+constexpr int WG_WAVES = 8;
+
+template <int H>
+__global__ void __launch_bounds__(64 * WG_WAVES) k_mlp_weight_grad(int n, long npad, int splits, const float *__restrict__ X,
+                                                         const float *__restrict__ Tt, const float *__restrict__ Y,
+                                                         const float *__restrict__ Z, const __bf16 *__restrict__ dzt,
+                                                         float *__restrict__ out) {
+    constexpr int HB = H / 32;
+    __shared__ float part[WG_WAVES][32 * 33];
+    const MlpView V = mlp_view(H);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
+    const int split = int(blockIdx.x) % splits;
+    int blk = int(blockIdx.x) / splits, l, ob, ib;  // layer, 32-row and 32-column block of its gradient
+    if (blk < HB) { l = 3; ob = 0; ib = blk; }
+    else if ((blk -= HB) < HB * HB) { l = 2; ob = blk / HB; ib = blk % HB; }
+    else if ((blk -= HB * HB) < HB * HB) { l = 1; ob = blk / HB; ib = blk % HB; }
+    else { l = 0; ob = blk - HB * HB; ib = 0; }
+    const int steps = int(npad / 32), per = (steps + splits - 1) / splits;
+    const int k0 = split * per, k1 = min(k0 + per, steps);
+    const float scale = 8.0f * float(n);
+    f32x4 acc[2][2] = {};
+#pragma unroll 2
+    for (int st = k0 + wave; st < k1; st += WG_WAVES) {
+        const int s = st * 32 + 8 * q;  // this lane's eight samples
+        bf16x8 av[2], bv[2];
+        if (l == 3) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                float dy = 0.0f;
+                if (r < MLP_OUT && s + j < n) {
+                    const size_t e = size_t(s + j) * MLP_OUT + r;
+                    dy = 2.0f * (Y[e] - Tt[e]) / scale;
+                }
+                av[0][j] = __bf16(dy);
+                av[1][j] = __bf16(0.0f);
+            }
+        } else {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                av[a] = *reinterpret_cast<const bf16x8 *>(dzt + (long(l) * H + ob * 32 + 16 * a + r) * npad + s);
+        }
+        const float *src = l == 0 ? X + r : Z + size_t(l - 1) * n * H + ib * 32 + r;
+        const int ld = l == 0 ? MLP_IN : H;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float v = s + j < n ? src[size_t(s + j) * ld + 16 * c] : 0.0f;
+                bv[c][j] = __bf16(l == 0 ? v : silu(v));
+            }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[a], bv[c], acc[a][c], 0, 0, 0);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[wave][(16 * a + 4 * q + i) * 33 + 16 * c + r] = acc[a][c][i];
+    __syncthreads();
+    float *dst = out + long(split) * mlp_params(H) + V.off_w[l];
+    for (int e = threadIdx.x; e < 1024; e += 64 * WG_WAVES) {
+        const int m = e >> 5, c = e & 31, o = ob * 32 + m;
+        if (o >= V.nout[l]) continue;
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < WG_WAVES; ++k) sum += part[k][m * 33 + c];
+        dst[long(o) * V.nin[l] + ib * 32 + c] = sum;
+    }
+}
+
+// Gradients from the partial sums: the first `wblocks` workgroups one weight per thread over the splits, the
+// others 16 bias columns each over the 16-sample tiles (sixteen interleaved partial sums, then those in order).
+template <int H>
+__global__ void __launch_bounds__(256) k_mlp_grad_sum(int wblocks, int splits, int tiles, const float *__restrict__ part,
+                                                      const float *__restrict__ dbias, float *__restrict__ grad) {
+    const MlpView V = mlp_view(H);
+    if (int(blockIdx.x) < wblocks) {
+        const long p = long(blockIdx.x) * 256 + threadIdx.x, np = mlp_params(H);
+        if (p >= np) return;
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (p >= V.off_b[l] && p < V.off_b[l] + V.nout[l]) return;
+        float s = 0.0f;
+        for (int k = 0; k < splits; ++k) s += part[long(k) * np + p];
+        grad[p] = s;
+        return;
+    }
+    __shared__ float sum[16][16];
+    const int col = threadIdx.x & 15, c = (int(blockIdx.x) - wblocks) * 16 + col, ph = threadIdx.x >> 4, cols = 3 * H + 8;
+    float s = 0.0f;
+    if (c < cols) {
+#pragma unroll 8
+        for (int t = ph; t < tiles; t += 16) s += dbias[long(t) * cols + c];
+    }
+    sum[ph][col] = s;
+    __syncthreads();
+    if (ph == 0 && c < cols) {
+        float total = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) total += sum[k][col];
+        const int l = c < 3 * H ? c / H : 3;
+        grad[V.off_b[l] + (c - l * H)] = total;
+    }
+}
+
 // dY = 2 (Y - T) / (8 n); also the per-sample squared error (for the loss)
 __global__ void k_loss_grad(int n, const float *__restrict__ Y, const float *__restrict__ Tt, float *__restrict__ dY,
                             float *__restrict__ sqerr) {
@@ -492,7 +813,10 @@ int32_t forward_h(const float *P, const uint16_t *Pb, int n, const float *X, flo
     const unsigned grid = blocks_for((n + 15) / 16, 4);
     const __bf16 *pb = reinterpret_cast<const __bf16 *>(Pb);
     if (mode == 0 && !Z) return infer_h<H, float>(P, Pb, n, X, Y, s);
-    if (mode == 0) k_mlp_forward<H, true><<<grid, 256, 0, s>>>(P, pb, n, X, Y, Z);
+    // (16-byte weight fragments)
+    if (mode == 0 && (reinterpret_cast<uintptr_t>(Pb) & 15u) == 0)
+        k_mlp_forward_save<H><<<blocks_for(n, 16), 256, 0, s>>>(P, pb, n, X, Y, Z);
+    else if (mode == 0) k_mlp_forward<H, true><<<grid, 256, 0, s>>>(P, pb, n, X, Y, Z);
     else k_mlp_forward<H, false><<<grid, 256, 0, s>>>(P, pb, n, X, Y, Z);
     return mcheck("mlp forward");
 }
@@ -519,6 +843,20 @@ int32_t scratch_address(float **out) {
     return BMHD_OK;
 }
 
+// The fused backward pass (BF16 products) on a work area of the layout b, 16-byte aligned.
+template <int H>
+int32_t backward_fused(const BackLayout &b, const float *P, int n, const float *X, const float *Tt, const float *Z,
+                       const float *Y, float *grad, float *sqerr, float *work, hipStream_t s) {
+    __bf16 *dzt = reinterpret_cast<__bf16 *>(work);
+    float *dbias = work + b.dbias, *part = b.splits > 1 ? work + b.part : grad;
+    const int tiles = int(b.npad / 16), hb = H / 32, blocks = 2 * hb + 2 * hb * hb;
+    const int wblocks = b.splits > 1 ? int(blocks_for(mlp_params(H), 256)) : 0;
+    k_mlp_back_chain<H><<<tiles, 256, 0, s>>>(P, n, b.npad, Tt, Y, Z, sqerr, dzt, dbias);
+    k_mlp_weight_grad<H><<<unsigned(blocks) * b.splits, 64 * WG_WAVES, 0, s>>>(n, b.npad, b.splits, X, Tt, Y, Z, dzt, part);
+    k_mlp_grad_sum<H><<<wblocks + blocks_for(3 * H + 8, 16), 256, 0, s>>>(wblocks, b.splits, tiles, part, dbias, grad);
+    return mcheck("mlp backward");
+}
+
 // Backward pass on a caller-supplied work area (bmhd_mlp_work_bytes(hidden, n) bytes); arguments checked
 // by the caller.
 int32_t backward_impl(const float *d_params, int32_t hidden, int32_t n, const float *d_x, const float *d_t,
@@ -527,6 +865,14 @@ int32_t backward_impl(const float *d_params, int32_t hidden, int32_t n, const fl
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int H = hidden;
     const MlpView V = mlp_view(H);
+    // BF16 products: the fused pass, unless the work area cannot hold its layout (its padding to 32 samples: up to
+    // 89 samples) or is not aligned for it; the products below also are the FP32 reference mode
+    const BackLayout lay = back_layout(H, n, bmhd_mlp_work_bytes(hidden, n) / sizeof(float));
+    if (mode == 0 && lay.splits && (reinterpret_cast<uintptr_t>(d_work) & 15u) == 0) {
+        if (H == 32) return backward_fused<32>(lay, d_params, n, d_x, d_t, d_save, d_y, d_grad, d_sqerr, d_work, s);
+        if (H == 64) return backward_fused<64>(lay, d_params, n, d_x, d_t, d_save, d_y, d_grad, d_sqerr, d_work, s);
+        return backward_fused<128>(lay, d_params, n, d_x, d_t, d_save, d_y, d_grad, d_sqerr, d_work, s);
+    }
     float *dY = d_work;                                  // [n][8]
     float *bufA = d_work + size_t(n) * 16;               // [n][H]
     float *bufB = bufA + size_t(n) * H;                  // [n][H]

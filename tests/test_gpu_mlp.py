@@ -95,3 +95,39 @@ def test_adam_matches_oracle(bd, oracle_mod):
     # the BF16 copy is the round-to-nearest of the FP32 master
     pb = net.pb.cpu().numpy().astype(np.uint16).astype(np.uint32) << 16
     assert np.abs(pb.view(np.float32) - got).max() <= np.abs(got).max() * 2 ** -8
+
+
+def _bf16(a):
+    return a.to(torch.bfloat16).double()
+
+
+@pytest.mark.parametrize("H,n", [(128, 1), (128, 160), (128, 161), (64, 129), (32, 97), (128, 4096), (32, 4127), (64, 16385)])
+def test_bf16_gradients_against_their_rounding_points(bd, H, n):
+    """The BF16 backward pass (fused or, for a work area too small for it, one product per launch) against the same
+    products in float64 with operands rounded to BF16 at the same points. The sums over n samples are FP32 (n 2^-24,
+    1e-3 at the largest n); a rounding that flips because a term differs by an FP32 unit changes that term by 2^-8,
+    a share of about 2^-14 of the terms. A missing 16-sample tile would show as sqrt(16 / n), 3e-2 or more."""
+    rng = np.random.default_rng(n)
+    npar = int(bd.lib().bmhd_mlp_n_params(H))
+    net = bd.Mlp(H, torch.from_numpy(rng.normal(scale=1.0 / np.sqrt(32), size=npar).astype(np.float32)))
+    x = torch.from_numpy(rng.normal(size=(n, 32)).astype(np.float32)).cuda()
+    t = torch.from_numpy(rng.normal(size=(n, 8)).astype(np.float32)).cuda()
+    y, z = net.forward(x, save=True)
+    _, g = net.loss_grad(x, t)
+    p, o, W = net.p, 0, []
+    for nout, nin in ((H, 32), (H, H), (H, H), (8, H)):
+        W.append((o, p[o:o + nout * nin].view(nout, nin)))
+        o += nout * nin + nout
+    d = 2.0 * (y - t) / (8.0 * n)
+    for l in (3, 2, 1, 0):
+        off, w = W[l]
+        a = x if l == 0 else z[l - 1] * torch.sigmoid(z[l - 1])
+        refs = ((off, _bf16(d).t() @ _bf16(a)), (off + w.numel(), d.double().sum(0)))
+        for at, ref in refs:
+            got = g[at:at + ref.numel()].double().view_as(ref)
+            err = float((got - ref).abs().max() / ref.abs().max())
+            print("rounded grad", H, n, l, tuple(ref.shape), err, flush=True)
+            assert err <= 2e-3, (l, tuple(ref.shape), err)
+        if l > 0:
+            s = torch.sigmoid(z[l - 1])
+            d = (_bf16(d) @ _bf16(w)).float() * (s * (1.0 + z[l - 1] * (1.0 - s)))
