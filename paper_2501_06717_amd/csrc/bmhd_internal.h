@@ -109,7 +109,6 @@ struct HostGrid {
     std::vector<int32_t> halo_items;
     std::vector<DevFcCell> fc_cells;
     int32_t n_halo_slots = 0, n_fc_rec = 0;
-    std::vector<int32_t> nbr;   // [nb][26][5]
     // workspace layout (byte offsets)
     size_t off_blocks = 0, off_sims = 0, off_lut = 0, off_order = 0, off_order_split = 0, off_halo_items = 0,
            off_fc_cells = 0;
@@ -127,6 +126,7 @@ struct HostGrid {
 };
 
 int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err);
+void neighbor_table(const HostGrid &g, int32_t *out);  // [nb][26][5]
 
 // BF16 inference of the flux-correction MLP on inputs already rounded to BF16 ([n][32], 16-byte
 // aligned), the same products as bmhd_mlp_forward in mode 0 on their FP32 originals; enqueued on stream.

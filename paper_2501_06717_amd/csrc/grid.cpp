@@ -11,7 +11,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <map>
 #include <numeric>
 
 #include "bmhd_internal.h"
@@ -47,9 +46,13 @@ bool wrap_block(const bmhd_sim_desc &s, int lvl, int axis, int64_t &c, int *bc_c
 }
 
 uint64_t spread3(uint64_t v) {
-    uint64_t r = 0;
-    for (int b = 0; b < 21; ++b) r |= ((v >> b) & 1ull) << (3 * b);
-    return r;
+    // 21 bits, two zeros between neighbours
+    v &= 0x1fffffull;
+    v = (v | v << 32) & 0x1f00000000ffffull;
+    v = (v | v << 16) & 0x1f0000ff0000ffull;
+    v = (v | v << 8) & 0x100f00f00f00f00full;
+    v = (v | v << 4) & 0x10c30c30c30c30c3ull;
+    return (v | v << 2) & 0x1249249249249249ull;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -64,6 +67,54 @@ void prim_to_cons_host(const double *w, double *u) {
     for (int a = 0; a < 3; ++a) u[1 + a] = rho * w[1 + a];
     for (int a = 0; a < 3; ++a) u[4 + a] = w[4 + a];
     u[7] = w[7] / (5.0 / 3.0 - 1.0) + 0.5 * rho * u2 + 0.5 * b2;
+}
+
+// The 26-direction neighbour table reported through the ABI; formed when it is asked for (nothing else reads it, and
+// it is half of the work of a grid).
+void neighbor_table(const HostGrid &g, int32_t *out) {
+    Lookup L{&g};
+    std::fill(out, out + size_t(g.nb) * NDIR * 5, -1);
+    for (int b = 0; b < g.nb; ++b) {
+        const int s = g.sim[b], l = g.level[b];
+        const bmhd_sim_desc &sd = g.sdesc[s];
+        int n = 0;
+        for (int dz = -1; dz <= 1; ++dz)
+            for (int dy = -1; dy <= 1; ++dy)
+                for (int dx = -1; dx <= 1; ++dx) {
+                    if (!dx && !dy && !dz) continue;
+                    int32_t *e = out + (size_t(b) * NDIR + n++) * 5;
+                    const int dd[3] = {dx, dy, dz};
+                    int64_t c[3];
+                    int code = -1;
+                    bool inside = true;
+                    for (int a = 0; a < 3 && inside; ++a) {
+                        c[a] = int64_t(g.ijk[3 * size_t(b) + a]) + dd[a];
+                        inside = wrap_block(sd, l, a, c[a], &code);
+                    }
+                    if (!inside) {
+                        e[0] = code == BMHD_BC_OUTFLOW ? BMHD_REL_OUTFLOW : BMHD_REL_INFLOW;
+                        continue;
+                    }
+                    int32_t id = L.at(s, l, c[0], c[1], c[2]);
+                    if (id >= 0) {
+                        e[0] = BMHD_REL_SAME;
+                        e[1] = id;
+                    } else if (l == 1) {
+                        e[0] = BMHD_REL_COARSER;
+                        e[1] = L.at(s, 0, c[0] >> 1, c[1] >> 1, c[2] >> 1);
+                    } else {
+                        e[0] = BMHD_REL_FINER;
+                        int m = 1;
+                        for (int q = 0; q < 8; ++q) {
+                            const int sub[3] = {q & 1, (q >> 1) & 1, q >> 2};
+                            bool touches = true;
+                            for (int a = 0; a < 3; ++a)
+                                if (dd[a] != 0 && sub[a] != (dd[a] > 0 ? 0 : 1)) touches = false;
+                            if (touches) e[m++] = L.at(s, 1, 2 * c[0] + sub[0], 2 * c[1] + sub[1], 2 * c[2] + sub[2]);
+                        }
+                    }
+                }
+    }
 }
 
 int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err) {
@@ -160,50 +211,6 @@ int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err) {
                 }
     }
 
-    // 26-direction neighbour table
-    g.nbr.assign(size_t(g.nb) * NDIR * 5, -1);
-    for (int b = 0; b < g.nb; ++b) {
-        const int s = g.sim[b], l = g.level[b];
-        const bmhd_sim_desc &sd = g.sdesc[s];
-        int n = 0;
-        for (int dz = -1; dz <= 1; ++dz)
-            for (int dy = -1; dy <= 1; ++dy)
-                for (int dx = -1; dx <= 1; ++dx) {
-                    if (!dx && !dy && !dz) continue;
-                    int32_t *e = &g.nbr[(size_t(b) * NDIR + n++) * 5];
-                    const int dd[3] = {dx, dy, dz};
-                    int64_t c[3];
-                    int code = -1;
-                    bool inside = true;
-                    for (int a = 0; a < 3 && inside; ++a) {
-                        c[a] = int64_t(g.ijk[3 * size_t(b) + a]) + dd[a];
-                        inside = wrap_block(sd, l, a, c[a], &code);
-                    }
-                    if (!inside) {
-                        e[0] = code == BMHD_BC_OUTFLOW ? BMHD_REL_OUTFLOW : BMHD_REL_INFLOW;
-                        continue;
-                    }
-                    int32_t id = L.at(s, l, c[0], c[1], c[2]);
-                    if (id >= 0) {
-                        e[0] = BMHD_REL_SAME;
-                        e[1] = id;
-                    } else if (l == 1) {
-                        e[0] = BMHD_REL_COARSER;
-                        e[1] = L.at(s, 0, c[0] >> 1, c[1] >> 1, c[2] >> 1);
-                    } else {
-                        e[0] = BMHD_REL_FINER;
-                        int m = 1;
-                        for (int q = 0; q < 8; ++q) {
-                            const int sub[3] = {q & 1, (q >> 1) & 1, q >> 2};
-                            bool touches = true;
-                            for (int a = 0; a < 3; ++a)
-                                if (dd[a] != 0 && sub[a] != (dd[a] > 0 ? 0 : 1)) touches = false;
-                            if (touches) e[m++] = L.at(s, 1, 2 * c[0] + sub[0], 2 * c[1] + sub[1], 2 * c[2] + sub[2]);
-                        }
-                    }
-                }
-    }
-
     // per-block face relations, halo slots and flux-correction records
     g.blocks.assign(size_t(g.nb), DevBlock{});
     g.halo_items.clear();
@@ -273,10 +280,13 @@ int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err) {
 
     // coarse cells that take flux corrections (faces in ascending order per cell)
     g.fc_cells.clear();
+    std::vector<DevFcCell> cells;  // one block's
+    int at[NCELL];                 // cell -> its entry
     for (int b = 0; b < g.nb; ++b) {
         const DevBlock &B = g.blocks[b];
         if (!B.fc_role) continue;
-        std::map<int, DevFcCell> cells;
+        std::fill(at, at + NCELL, -1);
+        cells.clear();
         for (int f = 0; f < 6; ++f) {
             if (!((B.fc_role >> f) & 1)) continue;
             const int a = f >> 1, side = f & 1;
@@ -288,22 +298,23 @@ int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err) {
                     ii[a1] = t1;
                     ii[a2] = t2;
                     const int cell = (ii[2] * 8 + ii[1]) * 8 + ii[0];
-                    auto it = cells.find(cell);
-                    if (it == cells.end()) {
+                    if (at[cell] < 0) {
+                        at[cell] = int(cells.size());
                         DevFcCell e;
                         std::memset(&e, 0, sizeof e);
                         e.block = b;
                         e.cell = cell;
-                        it = cells.emplace(cell, e).first;
+                        cells.push_back(e);
                     }
-                    DevFcCell &e = it->second;
+                    DevFcCell &e = cells[size_t(at[cell])];
                     e.rec[e.n] = B.fc_rec[f];
                     e.face[e.n] = f;
                     e.t[e.n] = t1 + 8 * t2;
                     e.n++;
                 }
         }
-        for (auto &kv : cells) g.fc_cells.push_back(kv.second);
+        for (int cell = 0; cell < NCELL; ++cell)
+            if (at[cell] >= 0) g.fc_cells.push_back(cells[size_t(at[cell])]);
     }
 
     // blocks whose cells or face ghosts can meet the body sphere

@@ -480,57 +480,122 @@ __global__ void __launch_bounds__(256) k_fill_view(Tables T, const double *__res
 // State remap after a refinement change: every cell of the new grid N takes the value that the ghost rules
 // of the old grid F give at its level and global index -- the leaf's own value (block unchanged), the
 // prolongation of a fine ghost cell (block refined from a level-0 parent) or the restriction of the 8
-// children (block coarsened). One workgroup per new block, one thread per cell; no contraction (inside
-// ghost_cell), so the result is exact to the oracle's.
+// children (block coarsened). One workgroup per new block, one thread per cell; which of the three holds is
+// one lookup per block. A copy streams the old block; a refined block stages the 4 x 4 x 4 coarse cells under it
+// and one layer across each face in LDS (160 cells through the ghost rules instead of seven per fine cell).
+// No contraction, so the result is exact to the oracle's. Bound by memory: 7,736 blocks from 6,784 in 92 us (158 us
+// with every cell through the general rule; the bytes at the copy rate take 90).
 __global__ void __launch_bounds__(512) k_remap(Tables F, const double *__restrict__ Uf, Tables N,
                                                double *__restrict__ Un) {
+#pragma clang fp contract(off)
+    __shared__ double sc[8][216];
     const int b = blockIdx.x, c = threadIdx.x;
     const DevBlock &B = N.blocks[b];
     const DevSim &S = F.sims[B.sim];
-    const Cursor cur{&F, Uf, size_t(F.nb) * 512};
-    const long long G[3] = {(long long)B.ijk[0] * 8 + (c & 7), (long long)B.ijk[1] * 8 + ((c >> 3) & 7),
-                            (long long)B.ijk[2] * 8 + (c >> 6)};
-    double u[8];
-    ghost_cell(cur, S, B.level, G, u);
-    const size_t vs = size_t(N.nb) * 512, off = size_t(b) * 512 + c;
+    const size_t vsf = size_t(F.nb) * 512, vs = size_t(N.nb) * 512;
+    double *dst = Un + size_t(b) * 512;
+    const int32_t same = lut_at(F, S, B.level, B.ijk[0], B.ijk[1], B.ijk[2]);
+    if (same >= 0) {
+        const double *src = Uf + size_t(same) * 512;
 #pragma unroll
-    for (int v = 0; v < 8; ++v) Un[v * vs + off] = u[v];
+        for (int v = 0; v < 8; ++v) (dst + v * vs)[unsigned(c)] = (src + v * vsf)[unsigned(c)];
+        return;
+    }
+    const Cursor cur{&F, Uf, vsf};
+    const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
+    double u[8];
+    if (B.level == 0) {
+        const long long G[3] = {(long long)B.ijk[0] * 8 + i, (long long)B.ijk[1] * 8 + j, (long long)B.ijk[2] * 8 + k};
+        restricted_cell(cur, S, G, u);
+    } else {
+        // coarse cells -1 .. 4 per axis around the block's corner, at most one coordinate outside 0 .. 3
+        if (c < 216) {
+            const int x = c % 6 - 1, y = (c / 6) % 6 - 1, z = c / 36 - 1;
+            const int out = ((unsigned)x > 3u) + ((unsigned)y > 3u) + ((unsigned)z > 3u);
+            if (out <= 1) {
+                long long G[3] = {(long long)B.ijk[0] * 4 + x, (long long)B.ijk[1] * 4 + y, (long long)B.ijk[2] * 4 + z};
+                coarse_cell(cur, S, G, u);
+#pragma unroll
+                for (int v = 0; v < 8; ++v) sc[v][c] = u[v];
+            }
+        }
+        __syncthreads();
+        const int at = ((k >> 1) + 1) * 36 + ((j >> 1) + 1) * 6 + (i >> 1) + 1;
+        const double sx = (i & 1) ? 0.25 : -0.25, sy = (j & 1) ? 0.25 : -0.25, sz = (k & 1) ? 0.25 : -0.25;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const double uc = sc[v][at];
+            double acc = uc + sx * minmod2(uc - sc[v][at - 1], sc[v][at + 1] - uc);
+            acc = acc + sy * minmod2(uc - sc[v][at - 6], sc[v][at + 6] - uc);
+            u[v] = acc + sz * minmod2(uc - sc[v][at - 36], sc[v][at + 36] - uc);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 8; ++v) (dst + v * vs)[unsigned(c)] = u[v];
 }
 
 // Refinement indicator per block: the largest normalised jump, over its cells and the three axes, of the
 // density and of |B|^2 between a cell's two face neighbours (neighbours outside the block by the ghost
-// rules): |q+ - q-| / (q+ + q- + 1e-300). One workgroup per block, one thread per cell. No contraction: the
-// value equals the host-side reference bit for bit.
+// rules): |q+ - q-| / (q+ + q- + 1e-300). One workgroup per block, one thread per cell: density and |B|^2 of the
+// block and of its six ghost faces (64 cells each, read in place from an equal-level neighbour, through the
+// ghost rules at a level change) go through LDS, so each value is loaded once: 6,784 blocks in 88 us (600 us with
+// every neighbour of every cell loaded by its thread, eight variables each). No contraction: the value equals the
+// host-side reference bit for bit.
 __global__ void __launch_bounds__(512) k_block_indicator(Tables T, const double *__restrict__ U, double *__restrict__ ind) {
 #pragma clang fp contract(off)
+    __shared__ double q[2][512], g[2][6][64];
     __shared__ double red[8];
     const int b = blockIdx.x, c = threadIdx.x;
     const DevBlock &B = T.blocks[b];
     const DevSim &S = T.sims[B.sim];
     const size_t vs = size_t(T.nb) * 512;
     const Cursor cur{&T, U, vs};
+    double rho, bx, by, bz;
+    auto cell = [&](const double *p) {
+        rho = p[0];
+        bx = p[4 * vs];
+        by = p[5 * vs];
+        bz = p[6 * vs];
+    };
+    cell(U + size_t(b) * 512 + c);
+    q[0][c] = rho;
+    q[1][c] = bx * bx + by * by + bz * bz;
+    const int f = __builtin_amdgcn_readfirstlane(c >> 6);
+    if (f < 6) {
+        // wavefront f: the ghost cells across face f
+        const int a = f >> 1, side = f & 1, t1 = c & 7, t2 = (c >> 3) & 7;
+        int n[3];
+        n[a] = side ? 8 : -1;
+        n[a == 0 ? 1 : 0] = t1;
+        n[a == 2 ? 1 : 2] = t2;
+        const int rel = B.face[f];
+        if (rel >= 0) {
+            cell(U + size_t(rel) * 512 + ((n[2] & 7) * 8 + (n[1] & 7)) * 8 + (n[0] & 7));
+        } else {
+            const long long G[3] = {(long long)B.ijk[0] * 8 + n[0], (long long)B.ijk[1] * 8 + n[1],
+                                    (long long)B.ijk[2] * 8 + n[2]};
+            double r1[1], b3[3];
+            ghost_cell<1>(cur, S, B.level, G, r1, 0);
+            ghost_cell<3>(cur, S, B.level, G, b3, 4);
+            rho = r1[0];
+            bx = b3[0];
+            by = b3[1];
+            bz = b3[2];
+        }
+        g[0][f][c & 63] = rho;
+        g[1][f][c & 63] = bx * bx + by * by + bz * bz;
+    }
+    __syncthreads();
     const int ii[3] = {c & 7, (c >> 3) & 7, c >> 6};
     double m = 0.0;
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-        double q[2][8];
-        for (int side = 0; side < 2; ++side) {
-            int n[3] = {ii[0], ii[1], ii[2]};
-            n[d] += side ? 1 : -1;
-            if ((unsigned)n[d] < 8u) {
-                const size_t off = size_t(b) * 512 + (n[2] * 8 + n[1]) * 8 + n[0];
-                for (int v = 0; v < 8; ++v) q[side][v] = U[v * vs + off];
-            } else {
-                const long long G[3] = {(long long)B.ijk[0] * 8 + n[0], (long long)B.ijk[1] * 8 + n[1],
-                                        (long long)B.ijk[2] * 8 + n[2]};
-                ghost_cell(cur, S, B.level, G, q[side]);
-            }
+        const int step = d == 0 ? 1 : (d == 1 ? 8 : 64), t = d == 0 ? ii[2] * 8 + ii[1] : (d == 1 ? ii[2] * 8 + ii[0] : ii[1] * 8 + ii[0]);
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const double qm = ii[d] == 0 ? g[v][2 * d][t] : q[v][c - step], qp = ii[d] == 7 ? g[v][2 * d + 1][t] : q[v][c + step];
+            m = fmax(m, fabs(qp - qm) / (qp + qm + 1e-300));
         }
-        const double rp = q[1][0], rm = q[0][0];
-        const double bp = q[1][4] * q[1][4] + q[1][5] * q[1][5] + q[1][6] * q[1][6];
-        const double bm = q[0][4] * q[0][4] + q[0][5] * q[0][5] + q[0][6] * q[0][6];
-        const double jr = fabs(rp - rm) / (rp + rm + 1e-300);
-        const double jb = fabs(bp - bm) / (bp + bm + 1e-300);
-        m = fmax(m, fmax(jr, jb));
     }
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
     if ((c & 63) == 0) red[c >> 6] = m;
@@ -1925,91 +1990,128 @@ __global__ void __launch_bounds__(576) k_face_targets(Tables F, const float *__r
     }
 }
 
-// Per-face training data of a whole block (one workgroup of 576 threads = one face per thread and
-// direction): stencil features in the face-normal frame (optionally z-scored) and the plain flux in the
-// face-normal frame, FP64 arithmetic.
-template <int FLUX>
-__global__ void __launch_bounds__(Slab<8>::NT) k_face_data(Tables T, StageArgs A, const float *__restrict__ stats,
-                                                           float *__restrict__ X, float *__restrict__ F) {
+// Four consecutive floats: one 16-byte store where the address allows it (uniform over a launch).
+__device__ __forceinline__ void store4(float *p, const float x[4]) {
+    if ((reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
+        *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) p[v] = x[v];
+    }
+}
+
+// Coordinates (x, y, z) of face f of direction D of a block, the one along D in 0 .. 8 (face_index's inverse).
+template <int D>
+__device__ __forceinline__ void face_coords(int f, int p[3]) {
+    if (D == 0) { p[0] = f % 9; p[1] = (f / 9) & 7; p[2] = f / 72; }
+    else if (D == 1) { p[0] = f & 7; p[1] = (f >> 3) % 9; p[2] = f / 72; }
+    else { p[0] = f & 7; p[1] = (f >> 3) & 7; p[2] = f >> 6; }
+}
+
+// Plain flux of face (i, j, k) of direction D of a block whose primitives are in LDS, in the face-normal frame, to
+// F[8] (see bmhd_face_data).
+template <int D, int FLUX>
+__device__ __forceinline__ void face_data_flux(double (*sW)[Slab<8>::NC], const DevBlock &B, const DevSim &S, bool near_body,
+                                               int i, int j, int k, float *__restrict__ F) {
     using SL = Slab<8>;
-    __shared__ double sW[8][SL::NC];
-    __shared__ unsigned char sM[SL::NC];
-    const int b = blockIdx.x;
-    double u[SL::NPT][8];
-    gather_issue<8>(T, A, b, 0, u);
-    gather_store<8, double>(T, b, 0, u, sW, sM);
-    __syncthreads();
+    int c[4];
+    bool in[4] = {false, false, false, false};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int n[3] = {i, j, k};
+        n[D] += q - 2;
+        c[q] = SL::idx(n[0], n[1], n[2]);
+        if (near_body) in[q] = in_body(S, B.level, B.ijk, n[0], n[1], n[2]);
+    }
+    double wl[8], wr[8], fl[8];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        const double q0 = sW[v][c[0]], q1 = sW[v][c[1]], q2 = sW[v][c[2]], q3 = sW[v][c[3]];
+        const double d0 = q1 - q0, d1 = q2 - q1, d2 = q3 - q2;
+        const double hl = (in[0] || in[2]) ? 0.0 : mc_half(d0, d1), hr = (in[1] || in[3]) ? 0.0 : mc_half(d1, d2);
+        wl[v] = q1 + hl;
+        wr[v] = q2 - hr;
+    }
+    if (in[2] && !in[1]) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) wr[v] = wl[v];
+        wr[1 + D] = -wl[1 + D];
+    } else if (in[1] && !in[2]) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) wl[v] = wr[v];
+        wl[1 + D] = -wr[1 + D];
+    }
+    num_flux<double, D, FLUX>(wl, wr, fl);
+    const bool none = in[1] && in[2];
+    float y[8];
+    y[0] = none ? 0.0f : float(fl[0]);
+    y[7] = none ? 0.0f : float(fl[7]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        y[1 + a] = none ? 0.0f : float(fl[1 + (D + a) % 3]);
+        y[4 + a] = none ? 0.0f : float(fl[4 + (D + a) % 3]);
+    }
+    F += (D * 576 + face_index<D>(i, j, k)) * 8;
+    store4(F, y);
+    store4(F + 4, y + 4);
+}
+
+// Stencil features of a block's faces of direction D to X (see bmhd_face_data): a thread takes four features of a
+// face at a time (half a stencil cell), so that a wavefront's stores are contiguous.
+template <int D>
+__device__ __forceinline__ void face_data_features(double (*sW)[Slab<8>::NC], const float *__restrict__ stats,
+                                                   float *__restrict__ X) {
+    for (int e = lane_tid(); e < 576 * 8; e += BLK_NT) {
+        const int q = (e >> 1) & 3, half = e & 1;
+        int n[3];
+        face_coords<D>(e >> 3, n);
+        n[D] += q - 2;
+        const int c = Slab<8>::idx(n[0], n[1], n[2]);
+        // (density, velocity) or (field, pressure)
+        float x[4] = {float(sW[half ? 4 + D : 0][c]), float(sW[half ? 4 + (D + 1) % 3 : 1 + D][c]),
+                      float(sW[half ? 4 + (D + 2) % 3 : 1 + (D + 1) % 3][c]), float(sW[half ? 7 : 1 + (D + 2) % 3][c])};
+        if (stats) {
+            const float *mean = stats + q * 8 + half * 4, *dev = mean + 32;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[v] = (x[v] - mean[v]) / dev[v];
+        }
+        store4(X + D * 576 * 32 + size_t(e) * 4, x);
+    }
+}
+
+// Per-face training data of a block: stencil features in the face-normal frame (optionally z-scored) and the plain
+// flux in the face-normal frame, FP64 arithmetic. One workgroup of eight wavefronts per block, gathered as in the
+// block form of the stage kernel (exactly 80 KiB of LDS, two workgroups per CU): each thread takes the low faces of
+// its cell, then three wavefronts the block's high faces of one direction each. Fluxes of 4,096 blocks 208 us (one
+// workgroup of 576 threads per block with a body mask beside the tile: 245), features of as many 370 us at 16-byte
+// pieces per lane (1,020 us with a face per lane, 128 bytes apart).
+template <int FLUX>
+__global__ void __launch_bounds__(BLK_NT, 4) k_face_data(Tables T, StageArgs A, const float *__restrict__ stats,
+                                                         float *__restrict__ X, float *__restrict__ F) {
+    __shared__ double sW[8][Slab<8>::NC];
+    const int wg = blockIdx.x, xcd = wg & 7;
+    const int b = T.order[xcd_first(T.nb, xcd) + (wg >> 3)];
     const DevBlock &B = T.blocks[b];
+    const DevSim &S = T.sims[B.sim];
     const bool near_body = (B.flags & BF_NEAR_BODY) != 0;
-    const int f = lane_tid();
-    if (f >= 576) return;
-#pragma unroll
-    for (int D = 0; D < 3; ++D) {
-        int i, j, k;
-        if (D == 0) { i = f % 9; j = (f / 9) & 7; k = f / 72; }
-        else if (D == 1) { i = f & 7; j = (f >> 3) % 9; k = f / 72; }
-        else { i = f & 7; j = (f >> 3) & 7; k = f >> 6; }
-        int c[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int o = q - 2;
-            c[q] = D == 0 ? SL::idx(i + o, j, k) : (D == 1 ? SL::idx(i, j + o, k) : SL::idx(i, j, k + o));
-        }
-        const size_t g = (size_t(b) * 3 + D) * 576 + f;
-        if (X) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float x[8];
-                x[0] = float(sW[0][c[q]]);
-                x[7] = float(sW[7][c[q]]);
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    x[1 + a] = float(sW[1 + (D + a) % 3][c[q]]);
-                    x[4 + a] = float(sW[4 + (D + a) % 3][c[q]]);
-                }
-#pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    const int e = q * 8 + v;
-                    X[g * 32 + e] = stats ? (x[v] - stats[e]) / stats[32 + e] : x[v];
-                }
-            }
-        }
-        if (F) {
-            double wl[8], wr[8], fl[8];
-            const bool m0 = near_body && sM[c[0]], m1 = near_body && sM[c[1]];
-            const bool m2 = near_body && sM[c[2]], m3 = near_body && sM[c[3]];
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                const double a = sW[v][c[0]], bb = sW[v][c[1]], cc = sW[v][c[2]], d = sW[v][c[3]];
-                const double d0 = bb - a, d1 = cc - bb, d2 = d - cc;
-                const double hl = (m0 || m2) ? 0.0 : mc_half(d0, d1), hr = (m1 || m3) ? 0.0 : mc_half(d1, d2);
-                wl[v] = bb + hl;
-                wr[v] = cc - hr;
-            }
-            if (m2 && !m1) {
-#pragma unroll
-                for (int v = 0; v < 8; ++v) wr[v] = wl[v];
-                wr[1 + D] = -wl[1 + D];
-            } else if (m1 && !m2) {
-#pragma unroll
-                for (int v = 0; v < 8; ++v) wl[v] = wr[v];
-                wl[1 + D] = -wr[1 + D];
-            }
-            if (D == 0) num_flux<double, 0, FLUX>(wl, wr, fl);
-            else if (D == 1) num_flux<double, 1, FLUX>(wl, wr, fl);
-            else num_flux<double, 2, FLUX>(wl, wr, fl);
-            if (m1 && m2) {
-#pragma unroll
-                for (int v = 0; v < 8; ++v) fl[v] = 0.0;
-            }
-            F[g * 8 + 0] = float(fl[0]);
-            F[g * 8 + 7] = float(fl[7]);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                F[g * 8 + 1 + a] = float(fl[1 + (D + a) % 3]);
-                F[g * 8 + 4 + a] = float(fl[4 + (D + a) % 3]);
-            }
-        }
+    gather_blk<double, false>(T, A, B, b, sW);
+    __syncthreads();
+    if (X) {
+        float *x = X + size_t(b) * 1728 * 32;
+        face_data_features<0>(sW, stats, x);
+        face_data_features<1>(sW, stats, x);
+        face_data_features<2>(sW, stats, x);
+    }
+    if (F) {
+        float *f = F + size_t(b) * 1728 * 8;
+        const int tid = lane_tid(), i = tid & 7, j = (tid >> 3) & 7;
+        const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+        face_data_flux<0, FLUX>(sW, B, S, near_body, i, j, w, f);
+        face_data_flux<1, FLUX>(sW, B, S, near_body, i, j, w, f);
+        face_data_flux<2, FLUX>(sW, B, S, near_body, i, j, w, f);
+        if (w == 0) face_data_flux<0, FLUX>(sW, B, S, near_body, 8, i, j, f);
+        else if (w == 1) face_data_flux<1, FLUX>(sW, B, S, near_body, i, 8, j, f);
+        else if (w == 2) face_data_flux<2, FLUX>(sW, B, S, near_body, i, j, 8, f);
     }
 }
 
@@ -2796,7 +2898,7 @@ int32_t bmhd_grid_info_get(const bmhd_grid *g, bmhd_grid_info *info) {
 
 int32_t bmhd_grid_neighbors(const bmhd_grid *g, int32_t *h_out) {
     if (!g || !h_out) return fail(BMHD_EINVAL, "null argument");
-    std::memcpy(h_out, g->h.nbr.data(), sizeof(int32_t) * g->h.nbr.size());
+    neighbor_table(g->h, h_out);
     return BMHD_OK;
 }
 
@@ -3008,8 +3110,8 @@ int32_t bmhd_face_data(const bmhd_grid *g, const double *d_U, int32_t flux, cons
     std::memset(&a, 0, sizeof a);
     a.Uin = d_U;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (flux == BMHD_FLUX_RUSANOV) k_face_data<BMHD_FLUX_RUSANOV><<<h.nb, Slab<8>::NT, 0, s>>>(h.dev, a, d_stats, d_X, d_F);
-    else k_face_data<BMHD_FLUX_HLLE><<<h.nb, Slab<8>::NT, 0, s>>>(h.dev, a, d_stats, d_X, d_F);
+    if (flux == BMHD_FLUX_RUSANOV) k_face_data<BMHD_FLUX_RUSANOV><<<h.nb, BLK_NT, 0, s>>>(h.dev, a, d_stats, d_X, d_F);
+    else k_face_data<BMHD_FLUX_HLLE><<<h.nb, BLK_NT, 0, s>>>(h.dev, a, d_stats, d_X, d_F);
     return launch_check("face_data");
 }
 
