@@ -395,6 +395,20 @@ int32_t bmhd_xchg_stage(const bmhd_xchg *x, int32_t r, int32_t stage, const doub
 int32_t bmhd_xchg_flux_correct(const bmhd_xchg *x, int32_t r, int32_t stage, double *d_Uout, const double *d_dt,
                                const bmhd_opts *o, int32_t *d_faults, void *stream);
 
+/* Every process's part at once (the processes of one GPU): bmhd_xchg_interior, then both passes' packs, transfers and
+ * unpacks (Sec. 4.4), one launch per kernel instead of one per process, the packs writing straight into the
+ * receivers' buffers. d_views holds the views one after another in process order (process r's starts at
+ * 8 * 1728 * (blocks of the processes before it) doubles), d_buf all receive buffers of a pass one after another (at least
+ * the larger pass's sum of h_len doubles; its contents are scratch). The views are those of the calls per process,
+ * bit for bit. */
+int32_t bmhd_xchg_all(const bmhd_xchg *x, const double *d_U, double *d_views, double *d_buf, int32_t *d_bad,
+                      void *stream);
+/* bmhd_xchg_stage for every process, then bmhd_xchg_flux_correct for every process: one stage of the whole grid from
+ * the views of bmhd_xchg_all. The same results bit for bit. */
+int32_t bmhd_xchg_stage_all(const bmhd_xchg *x, int32_t stage, const double *d_views, const double *d_U0,
+                            const double *d_Uin, double *d_Uout, const double *d_dt, const bmhd_opts *o,
+                            int32_t *d_faults, void *stream);
+
 /* ---------------------------------------------------------------------------------------------
  * Learned flux correction: a multilayer perceptron 32 -> H -> H -> H -> 8 with SiLU activations
  * (hidden width H in {32, 64, 128}). This component is not in the paper: it corrects the plain flux

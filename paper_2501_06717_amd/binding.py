@@ -26,7 +26,7 @@ EXPORTS = ["bmhd_version", "bmhd_last_error", "bmhd_grid_create", "bmhd_grid_des
            "bmhd_mlp_forward", "bmhd_mlp_backward", "bmhd_mlp_backward_noalloc", "bmhd_mlp_adam", "bmhd_mlp_to_bf16", "bmhd_face_data",
            "bmhd_block_indicator", "bmhd_adapt", "bmhd_xchg_create", "bmhd_xchg_destroy", "bmhd_xchg_sizes", "bmhd_xchg_messages", "bmhd_xchg_upload",
            "bmhd_xchg_interior", "bmhd_xchg_pack", "bmhd_xchg_unpack", "bmhd_xchg_stage", "bmhd_xchg_flux_correct",
-           "bmhd_face_targets", "bmhd_xchg_create_for_stage"]
+           "bmhd_face_targets", "bmhd_xchg_create_for_stage", "bmhd_xchg_all", "bmhd_xchg_stage_all"]
 
 
 class SimDesc(ctypes.Structure):
@@ -148,6 +148,10 @@ def lib():
     L.bmhd_face_targets.restype = i32
     L.bmhd_xchg_stage.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp, P(Opts), vp, vp]
     L.bmhd_xchg_stage.restype = i32
+    L.bmhd_xchg_all.argtypes = [vp, vp, vp, vp, vp, vp]
+    L.bmhd_xchg_all.restype = i32
+    L.bmhd_xchg_stage_all.argtypes = [vp, i32, vp, vp, vp, vp, vp, P(Opts), vp, vp]
+    L.bmhd_xchg_stage_all.restype = i32
     L.bmhd_xchg_flux_correct.argtypes = [vp, i32, i32, vp, vp, P(Opts), vp, vp]
     L.bmhd_xchg_flux_correct.restype = i32
     _lib = L
@@ -567,25 +571,32 @@ class Xchg:
                     recvs[r][ro:ro + n].copy_(sends[s][so:so + n])
                 so += n
 
+    def _buffers(self, device):
+        """(views of all processes one after another, receive buffers of the larger pass), uncleared: complete views
+        are written cell by cell, stage-mode views hold only what the stage reads from them."""
+        import torch
+        return (torch.empty(8 * 1728 * self.grid.nb, dtype=torch.float64, device=device),
+                torch.empty(max(int(self.len[0].sum()), int(self.len[1].sum())), dtype=torch.float64, device=device))
+
+    def _run(self, U, views, buf, bad=None, stream=None):
+        import torch
+        if tuple(U.shape) != (8, self.grid.nb, 8, 8, 8):
+            raise BmhdError("the state must be [8][n_blocks][8][8][8]")
+        _check(lib().bmhd_xchg_all(self.h, _dev_ptr(U, torch.float64), _dev_ptr(views),
+                                   _dev_ptr(buf) if buf.numel() else None,
+                                   _dev_ptr(bad, torch.int32) if bad is not None else None, _stream_ptr(stream)))
+
     def run(self, U, bad=None):
         """Both passes of the exchange for every process: returns the views (bad: optional int32 device
         counter of skipped messages)."""
-        import torch
-        # complete views: every cell is written below (interior, 26 directions of ghost cells), no clearing;
-        # stage-mode views hold only what the stage reads from them
-        views = [torch.empty((8, int(self.nloc[r]), 12, 12, 12), dtype=torch.float64, device=U.device)
-                 for r in range(self.nr)]
+        views, buf = self._buffers(U.device)
+        self._run(U, views, buf, bad)
+        out, at = [], 0
         for r in range(self.nr):
-            self.interior(r, U, views[r])
-        for p in (1, 2):
-            sends = [torch.empty(self.send_len(p, s), dtype=torch.float64, device=U.device) for s in range(self.nr)]
-            recvs = [torch.empty(self.recv_len(p, r), dtype=torch.float64, device=U.device) for r in range(self.nr)]
-            for s in range(self.nr):
-                self.pack(p, s, views[s], sends[s])
-            self.transfer(p, sends, recvs)
-            for r in range(self.nr):
-                self.unpack(p, r, recvs[r], views[r], bad=bad)
-        return views
+            n = 8 * 1728 * int(self.nloc[r])
+            out.append(views[at:at + n].view(8, int(self.nloc[r]), 12, 12, 12))
+            at += n
+        return out
 
     def stage(self, r, e, view, U0, Uin, Uout, dt, opts: Optional[Opts] = None, faults=None, stream=None, **kw):
         """Stage e (0 or 1) of process r's blocks, ghost cells from its exchanged view."""
@@ -617,16 +628,20 @@ class Xchg:
         both exchange passes into every process's view, each process's stage from its view, then the flux
         corrections. dt per step: the CFL minimum over all blocks (bmhd_reduce_dt, the stand-in for the
         reduction over processes). Returns the last step's dt."""
+        import torch
         o = make_opts(recompute_dt=False, cfl=cfl, **kw)
-        dt = None
+        state = (8, self.grid.nb, 8, 8, 8)
+        if tuple(U0.shape) != state or tuple(U1.shape) != state:
+            raise BmhdError(f"states must be {state}")
+        fp = _dev_ptr(faults, torch.int32) if faults is not None else ctypes.c_void_p(0)
+        dt, views, buf = None, *self._buffers(U0.device)
         for _ in range(n_steps):
             dt = self.grid.reduce_dt(U0, cfl)
             for e, (Uin, Uout) in enumerate(((U0, U1), (U1, U0))):
-                views = self.run(Uin)
-                for r in range(self.nr):
-                    self.stage(r, e, views[r], U0, Uin, Uout, dt, opts=o, faults=faults)
-                for r in range(self.nr):
-                    self.flux_correct(r, e, Uout, dt, opts=o, faults=faults)
+                self._run(Uin, views, buf)
+                _check(lib().bmhd_xchg_stage_all(self.h, e, _dev_ptr(views), _dev_ptr(U0, torch.float64),
+                                                 _dev_ptr(Uin, torch.float64), _dev_ptr(Uout, torch.float64),
+                                                 _dev_ptr(dt), ctypes.byref(o), fp, _stream_ptr()))
         return dt
 
 

@@ -138,13 +138,15 @@ void prim_to_cons_host(const double *w, double *u);
 // ghost exchange between processes. All pointers are device pointers into the exchange's workspace or
 // the caller's view.
 struct ViewStage {
-    const double *view;          // [8][n_local][12][12][12]
-    const int32_t *view_local;   // [nb]: each block's index in its process's view
+    const double *view;          // [8][n_local][12][12][12], or every process's view one after another
+    const int64_t *view_at;      // [nb][2]: the start of each block's padded cells in the views of all processes, one
+                                 // after another, and the variable stride of its process's view
+    int64_t view_shift;          // where `view` starts in them
     const int32_t *view_faces;   // [nb]: bit f set where face f's ghost cells come from the view (a neighbour
                                  // on another process or level); the others are read in place
-    int64_t view_vs;             // n_local * 1728
     const int32_t *split;        // the subset's blocks, those clear of any body first
     int32_t n_clear, n_total;
+    bool beside;                 // the few workgroups near a body on the grid's side stream (its one user's call)
     const DevFcCell *fc_cells;   // the subset's coarse cells that take flux corrections
     int32_t n_fc;
 };

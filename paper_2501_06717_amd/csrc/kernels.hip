@@ -798,12 +798,13 @@ struct StageArgs {
     const int32_t *sched;
     int32_t n_sched;
     // ghost cells from a padded view [8][n][12][12][12] (one process's blocks after the exchange between
-    // processes) instead of the neighbours' interiors, the boundary rules and the halo buffer: view_local[b]
-    // is block b's index in the view, view_vs its variable stride; null: the usual gather
+    // processes) instead of the neighbours' interiors, the boundary rules and the halo buffer: view_at[2 b] -
+    // view_shift is where block b's padded cells start in it, view_at[2 b + 1] their variable stride; null: the
+    // usual gather
     const double *view;
-    const int32_t *view_local;
+    const int64_t *view_at;
+    int64_t view_shift;
     const int32_t *view_faces;  // per block: bit f, face f's ghost cells from the view (others in place)
-    int64_t view_vs;
     // the coarse cells k_flux_correct takes: a list of n_fc_list cells, or null for all of T.fc_cells
     const DevFcCell *fc_list;
     int32_t n_fc_list;
@@ -1015,7 +1016,8 @@ __device__ __forceinline__ void gather_issue(const Tables &T, const StageArgs &A
     // view gather: the ghost cells of faces whose neighbour is on another process or level come from the
     // process's padded view (received messages, restrictions, prolongations); the rest is read in place
     const int vfaces = VIEW ? A.view_faces[b] : 0;
-    const double *vbase = VIEW ? A.view + size_t(A.view_local[b]) * 1728 : nullptr;
+    const double *vbase = VIEW ? A.view + (A.view_at[2 * size_t(b)] - A.view_shift) : nullptr;
+    const size_t vview = VIEW ? size_t(A.view_at[2 * size_t(b) + 1]) : 0;
 #pragma unroll
     for (int m = 0; m < NPT; ++m) {
         const int c = tid + m * NTH;
@@ -1032,7 +1034,7 @@ __device__ __forceinline__ void gather_issue(const Tables &T, const StageArgs &A
         size_t stride;
         if (VIEW && fd >= 0 && ((vfaces >> fd) & 1)) {
             p = vbase + ((z + 2) * 12 + (j + 2)) * 12 + (i + 2);
-            stride = size_t(A.view_vs);
+            stride = vview;
         } else if (rel >= 0 || rel == FACE_OUTFLOW) {
             int src = b, ii = i, jj = j, zz = z;
             if (rel >= 0) {
@@ -1572,9 +1574,9 @@ __device__ __forceinline__ void load_halo(const Tables &T, const StageArgs &A, c
     size_t stride = size_t(T.nb) * 512;
     unsigned at;
     if (VIEW && ((A.view_faces[b] >> fd) & 1)) {
-        p = A.view + size_t(A.view_local[b]) * 1728;
+        p = A.view + (A.view_at[2 * size_t(b)] - A.view_shift);
         at = unsigned(((z + 2) * 12 + (y + 2)) * 12 + (x + 2));
-        stride = size_t(A.view_vs);
+        stride = size_t(A.view_at[2 * size_t(b) + 1]);
     } else if (rel >= 0) {
         p = A.Uin + size_t(rel) * 512;
         at = unsigned(((z & 7) * 8 + (y & 7)) * 8 + (x & 7));
@@ -2578,9 +2580,15 @@ int32_t launch_view_stage(const HostGrid &h, const StageArgs &a, const ViewStage
     ac.n_sched = v.n_clear;
     an.sched = v.split + v.n_clear;
     an.n_sched = nn;
-    if (nn) k_stage_wp<4, R, FLUX, POWELL, false, false, true><<<nn * 2, Slab<4>::NT, 0, s>>>(h.dev, an);
+    // the few workgroups near a body beside the block form's launch, as in bmhd_advance, where the call is for the
+    // whole grid: processes stepped from several streams or threads share the grid but not its side stream
+    hipStream_t side = s;
+    if (v.beside && nn && v.n_clear)
+        if (int32_t rc = fork_side(h, s, side)) return rc;
+    if (nn) k_stage_wp<4, R, FLUX, POWELL, false, false, true><<<nn * 2, Slab<4>::NT, 0, side>>>(h.dev, an);
     if (v.n_clear) k_stage_blk<R, FLUX, POWELL, true><<<v.n_clear, BLK_NT, 0, s>>>(h.dev, ac);
-    return launch_check("stage kernel");
+    if (int32_t rc = launch_check("stage kernel")) return rc;
+    return join_side(h, s, side);
 }
 
 template <typename R, int FLUX>
@@ -2621,9 +2629,9 @@ int32_t stage_from_view_impl(const HostGrid &h, const ViewStage &v, int e, const
     a.use_u0 = o.alpha[e] != 0.0 ? 1 : 0;
     a.count_faults = (e == 1 && faults) ? 1 : 0;
     a.view = v.view;
-    a.view_local = v.view_local;
+    a.view_at = v.view_at;
+    a.view_shift = v.view_shift;
     a.view_faces = v.view_faces;
-    a.view_vs = v.view_vs;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (o.precision == BMHD_FP64) return launch_view_stage_f<double>(h, a, v, o, s);
     return launch_view_stage_f<float>(h, a, v, o, s);

@@ -17,7 +17,10 @@
 // inflow state).
 //
 // On one GPU the processes are virtual: every view lives in the same device memory and the buffers move
-// with device copies standing in for the point-to-point transfers. Copy, restriction and prolongation
+// with device copies standing in for the point-to-point transfers. bmhd_xchg_all and bmhd_xchg_stage_all run every
+// process's part in one launch per kernel, the packs writing straight into the receive buffers: at eight processes of
+// 512 blocks each kernel takes 5-30 us, so a step as eight launches per kernel and 56 copies per pass was bound by
+// launches (128^3 cells: 1.67 ms a step; 0.58 ms at once). Copy, restriction and prolongation
 // use the arithmetic of bmhd_fill_ghosts (no contraction), so the views equal its padded view bit for bit.
 #include <hip/hip_runtime.h>
 
@@ -46,9 +49,15 @@ struct DevMsg {
     int64_t off;          // start of the message in the sender's send buffer (pack) or the receiver's
                           // receive buffer (unpack); for local messages unused
     int32_t cfirst;       // cells of the messages before this one in its group (one workgroup's work)
-    int32_t pad;
+    int32_t proc;         // the process whose view it reads (sent and local messages) or writes (received ones)
+    int64_t roff;         // start of the message in the receive buffers of all processes, one after another
 };
-static_assert(sizeof(DevMsg) == 72, "DevMsg layout");
+static_assert(sizeof(DevMsg) == 80, "DevMsg layout");
+
+// Where each process's view starts in the views of all processes, one after another, and its variable stride.
+struct ProcView {
+    int64_t at, vs;
+};
 
 }  // namespace bmhd
 
@@ -84,6 +93,8 @@ struct bmhd_xchg {
     size_t work_bytes = 0;
     size_t off_msgs[2][3] = {}, off_grp[2][3] = {}, off_bnd[2] = {}, off_blocks = 0;
     size_t off_split = 0, off_local = 0, off_fc = 0, off_vfaces = 0, off_int = 0;
+    size_t off_proc = 0, off_rank = 0, off_vat = 0;                  // ProcView per process; per block: its process,
+                                                                     // {start in all views, variable stride}
     void *d_work = nullptr;
 };
 
@@ -293,11 +304,18 @@ __device__ __forceinline__ int group_msg(const DevMsg *__restrict__ msgs, int mi
 
 // Pack: the headers and values of every message of the group's sending block into the send buffer.
 __global__ void __launch_bounds__(256) k_xchg_pack(Tables T, const DevMsg *__restrict__ msgs,
-                                                   const int32_t *__restrict__ grp, XView S, double *__restrict__ buf) {
+                                                   const int32_t *__restrict__ grp, XView S, double *__restrict__ buf,
+                                                   const ProcView *__restrict__ procs) {
     const int m0 = grp[blockIdx.x], m1 = grp[blockIdx.x + 1];
+    // with procs: every process's groups, S is the views one after another, the messages go straight to their places
+    // in the receive buffers
+    if (procs) {
+        const ProcView v = procs[msgs[m0].proc];
+        S = XView{S.v + v.at, size_t(v.vs)};
+    }
     for (int mi = m0 + threadIdx.x; mi < m1; mi += blockDim.x) {
         const DevMsg &m = msgs[mi];
-        double *h = buf + m.off;
+        double *h = buf + (procs ? m.roff : m.off);
         h[0] = double(m.r_local);
         for (int a = 0; a < 3; ++a) {
             h[1 + a] = double(m.lo[a]);
@@ -313,7 +331,7 @@ __global__ void __launch_bounds__(256) k_xchg_pack(Tables T, const DevMsg *__res
         box_cell(m, q - m.cfirst, i, j, k);
         double u[8];
         message_value(T, m, S, i, j, k, u);
-        double *d = buf + m.off + XCHG_NC + size_t(q - m.cfirst) * 8;
+        double *d = buf + (procs ? m.roff : m.off) + XCHG_NC + size_t(q - m.cfirst) * 8;
 #pragma unroll
         for (int v = 0; v < 8; ++v) d[v] = u[v];
     }
@@ -324,14 +342,19 @@ __global__ void __launch_bounds__(256) k_xchg_pack(Tables T, const DevMsg *__res
 // counted map (a damaged buffer) is not unpacked and is counted in *bad.
 __global__ void __launch_bounds__(256) k_xchg_unpack(const DevMsg *__restrict__ msgs, const int32_t *__restrict__ grp,
                                                      const double *__restrict__ buf, double *__restrict__ view,
-                                                     size_t vs, int32_t *bad) {
+                                                     size_t vs, int32_t *bad, const ProcView *__restrict__ procs) {
     const int m0 = grp[blockIdx.x], m1 = grp[blockIdx.x + 1];
+    if (procs) {
+        const ProcView v = procs[msgs[m0].proc];
+        view += v.at;
+        vs = size_t(v.vs);
+    }
     const int total = msgs[m1 - 1].cfirst + msgs[m1 - 1].ncell;
     int mi = m0;
     for (int q = threadIdx.x; q < total; q += blockDim.x) {
         mi = group_msg(msgs, mi, q);
         const DevMsg &mm = msgs[mi];
-        const double *h = buf + mm.off;
+        const double *h = buf + (procs ? mm.roff : mm.off);
         const int lb = int(h[0]);
         DevMsg m;
         bool ok = lb == mm.r_local;
@@ -359,9 +382,14 @@ __global__ void __launch_bounds__(256) k_xchg_unpack(const DevMsg *__restrict__ 
 // ghosts; pass 2 reads level-0 blocks and writes level-1 ghosts: no cell is both read and written).
 __global__ void __launch_bounds__(256) k_xchg_local(Tables T, const DevMsg *__restrict__ msgs,
                                                     const int32_t *__restrict__ grp, double *__restrict__ view,
-                                                    size_t vs) {
-    const XView S{view, vs};
+                                                    size_t vs, const ProcView *__restrict__ procs) {
     const int m0 = grp[blockIdx.x], m1 = grp[blockIdx.x + 1];
+    if (procs) {
+        const ProcView v = procs[msgs[m0].proc];
+        view += v.at;
+        vs = size_t(v.vs);
+    }
+    const XView S{view, vs};
     const int total = msgs[m1 - 1].cfirst + msgs[m1 - 1].ncell;
     int mi = m0;
     for (int q = threadIdx.x; q < total; q += blockDim.x) {
@@ -382,9 +410,15 @@ __global__ void __launch_bounds__(256) k_xchg_local(Tables T, const DevMsg *__re
 // clamped to the block's boundary layer (periodic axes keep the index: those cells came by message).
 __global__ void __launch_bounds__(256) k_xchg_bounds(Tables T, const int32_t *__restrict__ blocks,
                                                      const int32_t *__restrict__ local_of, double *__restrict__ view,
-                                                     size_t vs) {
+                                                     size_t vs, const ProcView *__restrict__ procs,
+                                                     const int32_t *__restrict__ rank) {
     const int b = blocks[blockIdx.x];
     const int lb = local_of[blockIdx.x];
+    if (procs) {
+        const ProcView v = procs[rank[b]];
+        view += v.at;
+        vs = size_t(v.vs);
+    }
     const DevBlock &B = T.blocks[b];
     const DevSim &S = T.sims[B.sim];
     for (int c = threadIdx.x; c < 1728; c += blockDim.x) {
@@ -412,8 +446,15 @@ __global__ void __launch_bounds__(256) k_xchg_bounds(Tables T, const int32_t *__
 // A process's view with its blocks' interior cells from the global state.
 __global__ void __launch_bounds__(512) k_xchg_interior(const int32_t *__restrict__ blocks,
                                                        const int32_t *__restrict__ local, const double *__restrict__ U,
-                                                       size_t us, double *__restrict__ view, size_t vs) {
+                                                       size_t us, double *__restrict__ view, size_t vs,
+                                                       const ProcView *__restrict__ procs,
+                                                       const int32_t *__restrict__ rank) {
     const int b = blocks[blockIdx.x], lb = local[b], c = threadIdx.x;
+    if (procs) {
+        const ProcView v = procs[rank[b]];
+        view += v.at;
+        vs = size_t(v.vs);
+    }
     const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
     const size_t dst = size_t(lb) * 1728 + ((k + 2) * 12 + (j + 2)) * 12 + (i + 2);
 #pragma unroll
@@ -448,9 +489,9 @@ ViewStage view_stage(const bmhd_xchg *x, int r, const double *d_view) {
     const unsigned char *base = static_cast<const unsigned char *>(x->d_work);
     ViewStage v{};
     v.view = d_view;
-    v.view_local = reinterpret_cast<const int32_t *>(base + x->off_local);
+    v.view_at = reinterpret_cast<const int64_t *>(base + x->off_vat);
+    v.view_shift = int64_t(x->blocks_first[r]) * 8 * 1728;
     v.view_faces = reinterpret_cast<const int32_t *>(base + x->off_vfaces);
-    v.view_vs = int64_t(x->nloc[r]) * 1728;
     v.split = reinterpret_cast<const int32_t *>(base + x->off_split) + x->blocks_first[r];
     v.n_clear = x->n_clear[r];
     v.n_total = x->nloc[r];
@@ -581,6 +622,14 @@ int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bo
             }
         // absolute offsets: a sender's buffer holds its segments to the receivers in receiver order, a
         // receiver's buffer its segments from the senders in sender order
+        // (and the receive buffers of all processes one after another, for the exchange of all of them at once)
+        std::vector<int64_t> rseg(size_t(nr) * nr, 0);  // [receiver][sender]
+        int64_t all = 0;
+        for (int rp = 0; rp < nr; ++rp)
+            for (int sp = 0; sp < nr; ++sp) {
+                rseg[size_t(rp) * nr + sp] = all;
+                all += x->len[p][size_t(sp) * nr + rp];
+            }
         x->send_first[p].assign(size_t(nr) + 1, 0);
         x->recv_first[p].assign(size_t(nr) + 1, 0);
         x->loc_first[p].assign(size_t(nr) + 1, 0);
@@ -594,6 +643,8 @@ int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bo
             }
             for (int rp = 0; rp < nr; ++rp)
                 for (DevMsg d : incoming[rp][sp]) {
+                    d.roff = d.off + rseg[size_t(rp) * nr + sp];
+                    d.proc = sp;
                     d.off += seg[rp];
                     x->send[p].push_back(d);
                 }
@@ -603,13 +654,18 @@ int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bo
             int64_t acc = 0;
             for (int sp = 0; sp < nr; ++sp) {
                 for (DevMsg d : incoming[rp][sp]) {
+                    d.roff = d.off + rseg[size_t(rp) * nr + sp];
+                    d.proc = rp;
                     d.off += acc;
                     x->recv[p].push_back(d);
                 }
                 acc += x->len[p][size_t(sp) * nr + rp];
             }
             x->recv_first[p][rp + 1] = int64_t(x->recv[p].size());
-            for (const DevMsg &d : locv[rp]) x->loc[p].push_back(d);
+            for (DevMsg d : locv[rp]) {
+                d.proc = rp;
+                x->loc[p].push_back(d);
+            }
             x->loc_first[p][rp + 1] = int64_t(x->loc[p].size());
         }
         // groups: within each process's range, messages ordered by their block (the sending block for
@@ -696,6 +752,12 @@ int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bo
     off = align256(off + sizeof(int32_t) * std::max<size_t>(1, x->view_faces.size()));
     x->off_int = off;
     off = align256(off + sizeof(int32_t) * std::max<size_t>(1, x->int_blocks.size()));
+    x->off_proc = off;
+    off = align256(off + sizeof(ProcView) * size_t(nr));
+    x->off_rank = off;
+    off = align256(off + sizeof(int32_t) * std::max<size_t>(1, x->rank.size()));
+    x->off_vat = off;
+    off = align256(off + 2 * sizeof(int64_t) * std::max<size_t>(1, x->rank.size()));
     x->work_bytes = off;
     *out = x;
     return BMHD_OK;
@@ -753,6 +815,17 @@ int32_t bmhd_xchg_upload(bmhd_xchg *x, void *d_work, size_t work_bytes, void *st
     put(x->off_fc, x->fc.data(), sizeof(DevFcCell) * x->fc.size());
     put(x->off_vfaces, x->view_faces.data(), sizeof(int32_t) * x->view_faces.size());
     put(x->off_int, x->int_blocks.data(), sizeof(int32_t) * x->int_blocks.size());
+    std::vector<ProcView> procs(size_t(x->nr));
+    for (int r = 0; r < x->nr; ++r) procs[size_t(r)] = {x->blocks_first[r] * 8 * 1728, int64_t(x->nloc[r]) * 1728};
+    std::vector<int64_t> vat(2 * x->rank.size());
+    for (size_t b = 0; b < x->rank.size(); ++b) {
+        const ProcView &v = procs[size_t(x->rank[b])];
+        vat[2 * b] = v.at + int64_t(x->local[b]) * 1728;
+        vat[2 * b + 1] = v.vs;
+    }
+    put(x->off_proc, procs.data(), sizeof(ProcView) * procs.size());
+    put(x->off_rank, x->rank.data(), sizeof(int32_t) * x->rank.size());
+    put(x->off_vat, vat.data(), sizeof(int64_t) * vat.size());
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (int32_t rc = hip_ok(hipMemcpyAsync(d_work, blob.data(), x->work_bytes, hipMemcpyHostToDevice, s), "xchg upload"))
         return rc;
@@ -772,7 +845,7 @@ int32_t bmhd_xchg_interior(const bmhd_xchg *x, int32_t r, const double *d_U, dou
     const auto *blocks = reinterpret_cast<const int32_t *>(base + x->off_int) + x->int_first[r];
     const auto *local = reinterpret_cast<const int32_t *>(base + x->off_local);
     k_xchg_interior<<<unsigned(ni), 512, 0, reinterpret_cast<hipStream_t>(stream)>>>(
-        blocks, local, d_U, size_t(x->grid->h.nb) * 512, d_view, size_t(n) * 1728);
+        blocks, local, d_U, size_t(x->grid->h.nb) * 512, d_view, size_t(n) * 1728, nullptr, nullptr);
     return hip_ok(hipGetLastError(), "xchg interior");
 }
 
@@ -787,7 +860,7 @@ int32_t bmhd_xchg_pack(const bmhd_xchg *x, int32_t pass, int32_t s, const double
     const auto *msgs = reinterpret_cast<const DevMsg *>(base + x->off_msgs[p][0]);
     const auto *grp = reinterpret_cast<const int32_t *>(base + x->off_grp[p][0]) + g0;
     const XView S{d_view, size_t(x->nloc[s]) * 1728};
-    k_xchg_pack<<<unsigned(ng), 256, 0, reinterpret_cast<hipStream_t>(stream)>>>(x->grid->h.dev, msgs, grp, S, d_send);
+    k_xchg_pack<<<unsigned(ng), 256, 0, reinterpret_cast<hipStream_t>(stream)>>>(x->grid->h.dev, msgs, grp, S, d_send, nullptr);
     return hip_ok(hipGetLastError(), "xchg pack");
 }
 
@@ -805,18 +878,18 @@ int32_t bmhd_xchg_unpack(const bmhd_xchg *x, int32_t pass, int32_t r, const doub
         if (!aligned8(d_recv)) return set_last_error(BMHD_EINVAL, "xchg_unpack: null or misaligned receive buffer");
         k_xchg_unpack<<<unsigned(rn), 256, 0, st>>>(reinterpret_cast<const DevMsg *>(base + x->off_msgs[p][1]),
                                                    reinterpret_cast<const int32_t *>(base + x->off_grp[p][1]) + rg,
-                                                   d_recv, d_view, vs, d_bad);
+                                                   d_recv, d_view, vs, d_bad, nullptr);
     }
     const int64_t lg = x->grp_first[p][2][r], ln = x->grp_first[p][2][r + 1] - lg;
     if (ln)
         k_xchg_local<<<unsigned(ln), 256, 0, st>>>(x->grid->h.dev, reinterpret_cast<const DevMsg *>(base + x->off_msgs[p][2]),
                                                   reinterpret_cast<const int32_t *>(base + x->off_grp[p][2]) + lg,
-                                                  d_view, vs);
+                                                  d_view, vs, nullptr);
     const int64_t bf = x->bnd_first[p][r], bn = x->bnd_first[p][r + 1] - bf;
     if (bn) {
         const auto *bl = reinterpret_cast<const int32_t *>(base + x->off_bnd[p]);
         const size_t nb_all = x->bnd_blocks[p].size();
-        k_xchg_bounds<<<unsigned(bn), 256, 0, st>>>(x->grid->h.dev, bl + bf, bl + nb_all + bf, d_view, vs);
+        k_xchg_bounds<<<unsigned(bn), 256, 0, st>>>(x->grid->h.dev, bl + bf, bl + nb_all + bf, d_view, vs, nullptr, nullptr);
     }
     return hip_ok(hipGetLastError(), "xchg unpack");
 }
@@ -841,6 +914,60 @@ int32_t bmhd_xchg_flux_correct(const bmhd_xchg *x, int32_t r, int32_t stage, dou
     if (!aligned8(d_Uout) || !aligned8(d_dt)) return set_last_error(BMHD_EINVAL, "xchg_flux_correct: null or misaligned buffer");
     const ViewStage v = view_stage(x, r, nullptr);
     return flux_correct_subset(x->grid->h, v, stage, d_Uout, d_dt, *o, d_faults, stream);
+}
+
+int32_t bmhd_xchg_all(const bmhd_xchg *x, const double *d_U, double *d_views, double *d_buf, int32_t *d_bad,
+                      void *stream) {
+    if (int32_t rc = need_xchg(x, 1, 0)) return rc;
+    const HostGrid &h = x->grid->h;
+    if (h.nb == 0) return BMHD_OK;
+    const bool moves = !x->send[0].empty() || !x->send[1].empty();
+    if (!aligned8(d_U) || !aligned8(d_views) || (moves && !aligned8(d_buf)))
+        return set_last_error(BMHD_EINVAL, "xchg_all: null or misaligned buffer");
+    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    const unsigned char *base = static_cast<const unsigned char *>(x->d_work);
+    const auto *procs = reinterpret_cast<const ProcView *>(base + x->off_proc);
+    const auto *rank = reinterpret_cast<const int32_t *>(base + x->off_rank);
+    auto msgs = [&](int p, int kind) { return reinterpret_cast<const DevMsg *>(base + x->off_msgs[p][kind]); };
+    auto groups = [&](int p, int kind) { return reinterpret_cast<const int32_t *>(base + x->off_grp[p][kind]); };
+    if (!x->int_blocks.empty())
+        k_xchg_interior<<<unsigned(x->int_blocks.size()), 512, 0, st>>>(
+            reinterpret_cast<const int32_t *>(base + x->off_int), reinterpret_cast<const int32_t *>(base + x->off_local),
+            d_U, size_t(h.nb) * 512, d_views, 0, procs, rank);
+    for (int p = 0; p < 2; ++p) {
+        const size_t ns = x->grp[p][0].size() - 1, nr = x->grp[p][1].size() - 1, nl = x->grp[p][2].size() - 1;
+        if (ns) k_xchg_pack<<<unsigned(ns), 256, 0, st>>>(h.dev, msgs(p, 0), groups(p, 0), XView{d_views, 0}, d_buf, procs);
+        if (nr) k_xchg_unpack<<<unsigned(nr), 256, 0, st>>>(msgs(p, 1), groups(p, 1), d_buf, d_views, 0, d_bad, procs);
+        if (nl) k_xchg_local<<<unsigned(nl), 256, 0, st>>>(h.dev, msgs(p, 2), groups(p, 2), d_views, 0, procs);
+        const size_t bn = x->bnd_blocks[p].size();
+        if (bn) {
+            const auto *bl = reinterpret_cast<const int32_t *>(base + x->off_bnd[p]);
+            k_xchg_bounds<<<unsigned(bn), 256, 0, st>>>(h.dev, bl, bl + bn, d_views, 0, procs, rank);
+        }
+    }
+    return hip_ok(hipGetLastError(), "xchg all");
+}
+
+int32_t bmhd_xchg_stage_all(const bmhd_xchg *x, int32_t stage, const double *d_views, const double *d_U0,
+                            const double *d_Uin, double *d_Uout, const double *d_dt, const bmhd_opts *o,
+                            int32_t *d_faults, void *stream) {
+    if (int32_t rc = need_xchg(x, 1, 0)) return rc;
+    if (!o) return set_last_error(BMHD_EINVAL, "xchg_stage_all: null options");
+    const HostGrid &h = x->grid->h;
+    if (h.nb == 0) return BMHD_OK;
+    if (!aligned8(d_views) || !aligned8(d_U0) || !aligned8(d_Uin) || !aligned8(d_Uout) || !aligned8(d_dt))
+        return set_last_error(BMHD_EINVAL, "xchg_stage_all: null or misaligned buffer");
+    // the grid's own schedule (blocks clear of any body first) instead of one process's
+    ViewStage v = view_stage(x, 0, d_views);
+    v.split = h.dev.order_split;
+    v.n_clear = h.n_clear;
+    v.n_total = h.nb;
+    v.beside = true;
+    v.n_fc = 0;
+    if (int32_t rc = stage_from_view(h, v, stage, d_U0, d_Uin, d_Uout, d_dt, *o, d_faults, stream)) return rc;
+    v.fc_cells = h.dev.fc_cells;
+    v.n_fc = h.dev.n_fc_cells;
+    return flux_correct_subset(h, v, stage, d_Uout, d_dt, *o, d_faults, stream);
 }
 
 }  // extern "C"

@@ -205,3 +205,44 @@ def test_sharded_stage_refuses_what_it_does_not_take(bd):
         x.stage(0, 0, view, U, U, torch.empty_like(U), dt, local_dt=True)
     with pytest.raises(bd.BmhdError):
         x.stage(0, 0, view, U, U, torch.empty_like(U), dt, persist_wgs=256)
+
+
+@pytest.mark.parametrize("for_stage", [False, True])
+@pytest.mark.parametrize("kind", ["one", "random3", "gaps", "each"])
+@pytest.mark.parametrize("grid", ["odd_box_mixed_bc", "two_level_mixed_bc", "magnetosphere_cut"])
+def test_calls_per_process_equal_the_call_for_all(bd, grid, kind, for_stage):
+    """The exchange and a stage called process by process, with a send and a receive buffer each, against
+    the calls that run every process's part in one launch per kernel: bit for bit, also where processes
+    own no block."""
+    wl = GRIDS[grid]()
+    rank, n = ranks(wl, "random3" if kind == "gaps" else kind, seed=len(grid))
+    if kind == "gaps":
+        rank, n = (2 * rank + 1).astype(np.int32), 7
+    print("per process", grid, kind, for_stage, n, "processes", wl.n_blocks, "blocks", flush=True)
+    g = bd.Grid.from_workload(wl).upload()
+    x = bd.Xchg(g, rank, n, for_stage=for_stage).upload()
+    U = g.set_state(torch.from_numpy(wk.random_positive_state(wl, seed=5)).cuda())
+    views = [x.new_view(r) for r in range(n)]
+    for r in range(n):
+        x.interior(r, U, views[r])
+    for p in (1, 2):
+        sends = [torch.empty(x.send_len(p, s), dtype=torch.float64, device="cuda") for s in range(n)]
+        recvs = [torch.empty(x.recv_len(p, r), dtype=torch.float64, device="cuda") for r in range(n)]
+        for s in range(n):
+            x.pack(p, s, views[s], sends[s])
+        x.transfer(p, sends, recvs)
+        for r in range(n):
+            x.unpack(p, r, recvs[r], views[r])
+    if not for_stage:                          # stage-mode views hold only what the stage reads
+        for a, b in zip(views, x.run(U)):
+            assert a.shape == b.shape and torch.equal(a, b)
+    kw = dict(flux="hlle", powell=True)
+    dt = g.reduce_dt(U, 0.8)
+    one, whole = torch.empty_like(U), torch.empty_like(U)
+    for r in range(n):
+        x.stage(r, 0, views[r], U, U, one, dt, **kw)
+    for r in range(n):
+        x.flux_correct(r, 0, one, dt, **kw)
+    x.advance(U.clone(), whole, 1, cfl=0.8, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(one, whole)             # the first stage's state of the step
