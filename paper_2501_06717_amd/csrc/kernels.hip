@@ -876,6 +876,25 @@ struct BitMask {
     __device__ __forceinline__ bool operator()(int c) const { return (m[c >> 5] >> (c & 31)) & 1u; }
 };
 
+// Record the flux of face (t1, t2) of block face bf if that takes part in a flux correction; component v of the
+// flux is comp(v) in x, y, z.
+template <typename R, typename Comp>
+__device__ __forceinline__ void record_block_face(const Tables &T, const DevBlock &B, int bf, int t1, int t2,
+                                                  const R fl[8], Comp comp) {
+    if (bf >= 0 && B.fc_rec[bf] >= 0) {
+        double *rec = T.fcbuf + size_t(B.fc_rec[bf]) * FC_REC;
+        if ((B.fc_role >> bf) & 1) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) rec[comp(v) * 64 + t2 * 8 + t1] = double(fl[v]);
+        } else {
+            const int q = B.fc_quad[bf];
+            const int g1 = 8 * (q & 1) + t1, g2 = 8 * (q >> 1) + t2;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) rec[FC_COARSE + comp(v) * 256 + g2 * 16 + g1] = double(fl[v]);
+        }
+    }
+}
+
 // Record the flux of a face of direction D, (i, j, z) block-local (the face between cells (i-1, j, z) and
 // (i, j, z) for D = 0, likewise j and z), if it lies on a block face that takes part in a flux correction.
 template <int D, typename R>
@@ -884,18 +903,7 @@ __device__ __forceinline__ void record_fc(const Tables &T, const DevBlock &B, in
     if (D == 0) { if (i == 0) bf = 0; else if (i == 8) bf = 1; t1 = j; t2 = z; }
     if (D == 1) { if (j == 0) bf = 2; else if (j == 8) bf = 3; t1 = i; t2 = z; }
     if (D == 2) { if (z == 0) bf = 4; else if (z == 8) bf = 5; t1 = i; t2 = j; }
-    if (bf >= 0 && B.fc_rec[bf] >= 0) {
-        double *rec = T.fcbuf + size_t(B.fc_rec[bf]) * FC_REC;
-        if ((B.fc_role >> bf) & 1) {
-#pragma unroll
-            for (int v = 0; v < 8; ++v) rec[v * 64 + t2 * 8 + t1] = double(fl[v]);
-        } else {
-            const int q = B.fc_quad[bf];
-            const int g1 = 8 * (q & 1) + t1, g2 = 8 * (q >> 1) + t2;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) rec[FC_COARSE + v * 256 + g2 * 16 + g1] = double(fl[v]);
-        }
-    }
+    record_block_face(T, B, bf, t1, t2, fl, [](int v) { return v; });
 }
 
 // Flux through one face of direction D of a slab whose primitives are in LDS: the face between cells
@@ -1547,18 +1555,19 @@ __global__ void __launch_bounds__(64 * (KS + 1), (wp_waves_per_simd<KS, R>())) k
 // ------------------------------------------------------------------------------------------------
 // Block form of the stage kernel: one workgroup of eight wavefronts per 8x8x8 block clear of any body,
 // wavefront k owning cell layer k (lane = (i, j)). Each wavefront computes the low-side face of each of
-// its cells in x, y and z, as the plane form does, and, in one more pass with the direction chosen per
-// lane, its layer's eight faces at x = 8 and eight at y = 8 (each evaluated in the lane whose cell it
-// bounds) plus eight of the block's 64 faces at z = 8: every wavefront does four face passes and no
-// wavefront is set aside for the high faces. Flux differences enter each cell's sums as two multiply-adds
-// (low side, then high side). LDS holds exactly the block and its face halos (80 KiB in FP64): the z
-// fluxes travel through the x/y halo space and the top halo layer once those are dead, and the
-// end-of-step reduction reuses the bottom halo layers, so two workgroups (sixteen wavefronts) share a
-// CU (the plane form on 8x8x4 slabs: ten). Blocks near a body run on the plane form in a second launch.
+// its cells in x, y and z, as the plane form does; the block's 64 faces at x = 8, at y = 8 and at z = 8 are one more
+// pass of the wavefronts of layers 3, 4 and 5: 27 face passes a block. (As a pass of eight x, eight y and eight z
+// faces in each wavefront, direction by lane, they were 32 passes, 24 of 64 lanes in use in eight of them.) Flux
+// differences enter each cell's sums as two multiply-adds (low side, then high side). LDS holds exactly the block and
+// its face halos (80 KiB in FP64): the z fluxes and the high faces' fluxes travel through the halo space once that is
+// dead, so two workgroups (sixteen wavefronts) share a CU (the plane form on 8x8x4 slabs: ten). Layers 3-5 read no
+// halo cell for z, so their own z pass comes after. Blocks near a body run on the plane form in a second launch.
 // It is bound by VALU issue (80 % of the cycles): what counts is instructions. Sources that are uniform over a
 // wavefront (one face's halo per load), LDS indices by selects instead of the general slab numbering's
 // branches, the flux of num_flux64 and the limiter of mc_half took it from 2,126 to 1,718 instructions per
-// wavefront and the 256^3 wind's step from 2.55 to 2.2 ms (FP32 fluxes: 1.78 to 1.58 ms).
+// wavefront and the 256^3 wind's step from 2.55 to 2.2 ms (FP32 fluxes: 1.78 to 1.58 ms), the high faces' own
+// wavefronts to 1,420 and 2.05 ms (1.52 ms; 1,334 instructions). A raised priority for those wavefronts, or other
+// layers for every other block, made no difference.
 
 constexpr int BLK_NT = 512;
 
@@ -1636,51 +1645,24 @@ __device__ __forceinline__ void gather_blk(const Tables &T, const StageArgs &A, 
     if (w < 4) store(u2, c2);
 }
 
-// Rotate the vector components of a state into the frame of normal direction d (normal first, then the
-// other two in cyclic order), d chosen per lane.
-template <typename R>
-__device__ __forceinline__ void rotate_in(int d, R w[8]) {
-#pragma unroll
-    for (int base = 1; base <= 4; base += 3) {
-        const R x = w[base], y = w[base + 1], z = w[base + 2];
-        w[base] = d == 0 ? x : (d == 1 ? y : z);
-        w[base + 1] = d == 0 ? y : (d == 1 ? z : x);
-        w[base + 2] = d == 0 ? z : (d == 1 ? x : y);
-    }
-}
-
 // Flux of direction D through the face between the cells at LDS indices c[1] and c[2], away from any body cell,
-// and the face-averaged normal field. With ROT the face is in the frame of direction d, chosen per lane: the
-// face states are reconstructed component by component (the limiter acts on each component alone) and then
-// rotated, so one x-normal evaluation serves every direction, and the flux comes out in that frame.
+// and the face-averaged normal field. With ROT component v is read from sW[comp[v]] (uniform over the wavefront):
+// with the vector components in normal-first order one x-normal evaluation serves every direction, and the flux
+// comes out in that frame.
 template <typename R, int D, int FLUX, bool ROT = false>
-__device__ __forceinline__ void blk_face(R (*sW)[Slab<8>::NC], const int (&c)[4], R (&f)[8], R &bbar, int d = 0) {
+__device__ __forceinline__ void blk_face(R (*sW)[Slab<8>::NC], const int (&c)[4], R (&f)[8], R &bbar,
+                                         const int *comp = nullptr) {
     R wl[8], wr[8];
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
-        const R a = sW[v][c[0]], b = sW[v][c[1]], cc = sW[v][c[2]], dd = sW[v][c[3]];
+        const R *p = sW[ROT ? comp[v] : v];
+        const R a = p[c[0]], b = p[c[1]], cc = p[c[2]], dd = p[c[3]];
         const R d0 = b - a, d1 = cc - b, d2 = dd - cc;
         wl[v] = b + mc_half(d0, d1);
         wr[v] = cc - mc_half(d1, d2);
     }
-    if constexpr (ROT) {
-        rotate_in(d, wl);
-        rotate_in(d, wr);
-    }
     num_flux<R, D, FLUX>(wl, wr, f);
     bbar = R(0.5) * (wl[4 + D] + wr[4 + D]);
-}
-
-// Flux of a face of direction D from the rotated frame of blk_face back to x, y, z.
-template <int D, typename R>
-__device__ __forceinline__ void unrotate(const R fr[8], R f[8]) {
-    f[0] = fr[0];
-    f[7] = fr[7];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        f[1 + (D + a) % 3] = fr[1 + a];
-        f[4 + (D + a) % 3] = fr[4 + a];
-    }
 }
 
 // The value of the next lane (lane + 1) within each row of 16 lanes (DPP row shift; the last lane of a row
@@ -1692,16 +1674,7 @@ __device__ __forceinline__ double lane_next(double x) {
     const int lo = dpp_next(int(v)), hi = dpp_next(int(v >> 32));
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
-__device__ __forceinline__ double lane_read(double x, int l) {
-    const long long v = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane(int(v), l), hi = __builtin_amdgcn_readlane(int(v >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-__device__ __forceinline__ float lane_read(float x, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
-
-// The four face passes, the source and the update of one block whose primitives are in LDS.
+// The face passes, the source and the update of one block whose primitives are in LDS.
 template <typename R, int FLUX, bool POWELL>
 __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A, const DevBlock &B, int b,
                                             R (*sW)[Slab<8>::NC], double inv_dx, bool fc) {
@@ -1753,99 +1726,70 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         divb = fma(double(g), wy, divb);
     }
 
-    // high faces: lane (7, j) takes face x = 8 of row j, lane (i, 7) face y = 8 of column i (i < 7; lane
-    // (6, 6) takes column 7 for lane (7, 7)), lanes 0-6 and 8 eight faces z = 8 (row j = w of the top face
-    // layer); the other lanes repeat face x = 8 of row 0
-    R zf[8], zb;
-    {
-        int d = 0, in = w * 64 + 6, st = 1, out = SL::XH + w * 32 + 2, so = 1, fi = 0;
-        if (ci == 7) {
-            in += cj * 8;
-            out += cj * 4;
-        } else if (cj == 7 || l == 54) {
-            d = 1;
-            fi = cj == 7 ? ci : 7;
-            in = w * 64 + 48 + fi;
-            st = so = 8;
-            out = SL::YH + w * 32 + 16 + fi;
-        } else if (l < 7 || l == 8) {
-            d = 2;
-            fi = l == 8 ? 7 : l;
-            in = 6 * 64 + w * 8 + fi;
-            st = so = 64;
-            out = SL::ZHI + w * 8 + fi;
-        }
-        const int c[4] = {in, in + st, out, out + so};
-        R fr[8], bf;  // the flux in the face-normal frame
-        blk_face<R, 0, FLUX, true>(sW, c, fr, bf, d);
-        // the y = 8 face of column 7 moves from lane 54 to lane 63
-        R yr[8], yb;
-#pragma unroll
-        for (int v = 0; v < 8; ++v) yr[v] = lane_read(fr[v], 54);
-        yb = lane_read(bf, 54);
-        if (ci == 7) {
-            R fx[8];
-            unrotate<0>(fr, fx);
-#pragma unroll
-            for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(fx[v]), inv_dx, rhs[v]);
-            divb = fma(double(bf), inv_dx, divb);
-            if (fc) record_fc<0>(T, B, 8, cj, w, fx);
-        }
-        if (cj == 7) {
-            R fy[8];
-            if (ci == 7) unrotate<1>(yr, fy);
-            else unrotate<1>(fr, fy);
-            const R by = ci == 7 ? yb : bf;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(fy[v]), inv_dx, rhs[v]);
-            divb = fma(double(by), inv_dx, divb);
-            if (fc) record_fc<1>(T, B, ci, 8, w, fy);
-        }
-        if (l < 7 || l == 8) {
-            unrotate<2>(fr, zf);
-            zb = bf;
-            if (fc) record_fc<2>(T, B, fi, w, 8, zf);
-        }
-    }
-    // past this barrier the x/y halos and the top halo layer (z = 9) are dead: the z fluxes of face layers
-    // 1-8 go to the x/y halo space of each variable (64 per layer), their normal field to the top layer
-    __syncthreads();
-    R *zbar = &sW[0][0] + SL::ZHI + 64;  // [face layer - 1] strided by NC, 64 lanes each
-    if (l < 7 || l == 8) {
-        const int q = 7 * 64 + w * 8 + (l == 8 ? 7 : l);
-#pragma unroll
-        for (int v = 0; v < 8; ++v) sW[v][SL::XH + q] = zf[v];
-        zbar[7 * SL::NC + w * 8 + (l == 8 ? 7 : l)] = zb;
-    }
-    {
+    // z: the low-z face of each cell, or first, in the wavefronts of layers 3, 4 and 5, the block's 64 faces at
+    // x = 8, y = 8 and z = 8. Their own z pass follows the barrier: it reads no halo cell
+    const int hd = w - 3;
+    const bool high = unsigned(hd) < 3u;
+    auto z_pass = [&]() {
         // cell layers w - 2 .. w + 1, uniform over the wavefront (below the block: ZLO; above: ZHI = 8 layers on)
         const int c[4] = {(w < 2 ? SL::ZLO + w * 64 : (w - 2) * 64) + l, (w < 1 ? SL::ZLO + 64 : (w - 1) * 64) + l, tid,
                           (w > 6 ? SL::ZHI : (w + 1) * 64) + l};
         blk_face<R, 2, FLUX>(sW, c, f, bb);
         if (fc) record_fc<2>(T, B, ci, cj, w, f);
-    }
 #pragma unroll
-    for (int v = 0; v < 8; ++v) rhs[v] = fma(double(f[v]), inv_dx, rhs[v]);
-    divb = fma(-double(bb), inv_dx, divb);
+        for (int v = 0; v < 8; ++v) rhs[v] = fma(double(f[v]), inv_dx, rhs[v]);
+        divb = fma(-double(bb), inv_dx, divb);
+    };
+    // past the barrier the halos are dead: each variable's 768 cells take the fluxes of z face layers 1-8 (64 per
+    // layer), x = 8 and y = 8, and the first five variables' last 128 cells their normal fields, 128 each
+    R *ex = &sW[0][SL::ZLO];
+    const int zq = (w - 1) * 64;  // the place of this layer's low z faces
+    auto hand_over = [&](int v, int q, R x) { ex[v * SL::NC + q + l] = x; };
+    auto hand_over_field = [&](int q, R x) { ex[(q >> 7) * SL::NC + 640 + (q & 64) + l] = x; };
+    const int n1 = 1 + hd, t1 = hd < 2 ? 2 + hd : 1, t2 = hd < 1 ? 3 : hd;  // normal first, in cyclic order
+    const int comp[8] = {0, n1, t1, t2, n1 + 3, t1 + 3, t2 + 3, 7};
+    if (high) {
+        const int st = hd == 0 ? 1 : (hd == 1 ? 8 : 64);
+        const int in = hd == 0 ? l * 8 + 6 : (hd == 1 ? cj * 64 + 48 + ci : 384 + l);
+        const int out = hd == 0 ? SL::XH + l * 4 + 2 : (hd == 1 ? SL::YH + cj * 32 + 16 + ci : SL::ZHI + l);
+        const int c[4] = {in, in + st, out, out + st};
+        blk_face<R, 0, FLUX, true>(sW, c, f, bb, comp);
+        if (fc) record_block_face(T, B, 2 * hd + 1, ci, cj, f, [&](int v) { return comp[v]; });
+    } else {
+        z_pass();
+    }
+    __syncthreads();
+    if (high) {
+        const int q = hd == 0 ? 512 : (hd == 1 ? 576 : 448);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) hand_over(comp[v], q, f[v]);
+        hand_over_field(q, bb);
+        z_pass();
+    }
     if (w > 0) {
 #pragma unroll
-        for (int v = 0; v < 8; ++v) sW[v][SL::XH + (w - 1) * 64 + l] = f[v];
-        zbar[(w - 1) * SL::NC + l] = bb;
+        for (int v = 0; v < 8; ++v) hand_over(v, zq, f[v]);
+        hand_over_field(zq, bb);
     }
-    auto top_in = [&]() {  // the flux and normal field of each cell's high z face
+    auto high_in = [&]() {  // the fluxes and normal fields of each cell's high faces that other wavefronts computed
+        auto take = [&](int q) {
 #pragma unroll
-        for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(sW[v][SL::XH + w * 64 + l]), inv_dx, rhs[v]);
-        divb = fma(double(zbar[w * SL::NC + l]), inv_dx, divb);
+            for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(ex[v * SL::NC + q]), inv_dx, rhs[v]);
+            divb = fma(double(ex[(q >> 7) * SL::NC + 640 + (q & 127)]), inv_dx, divb);
+        };
+        take(w * 64 + l);
+        if (ci == 7) take(512 + w * 8 + cj);
+        if (cj == 7) take(576 + w * 8 + ci);
     };
-    // the bottom halo layers are dead past the next barrier: the end-of-step reduction uses them
-    double *red = reinterpret_cast<double *>(&sW[0][SL::ZLO]);
-    int *redi = reinterpret_cast<int *>(&sW[1][SL::ZLO]);
+    // the end-of-step reduction, in cells that hold no flux
+    double *red = reinterpret_cast<double *>(&sW[5][SL::ZLO + 640]);
+    int *redi = reinterpret_cast<int *>(&sW[6][SL::ZLO + 640]);
     const size_t vs = size_t(T.nb) * 512, off0 = size_t(b) * 512;
     if constexpr (sizeof(R) == 4) {
         // sized for 80 registers: everything is loaded where it is used (with the FP64 form's early loads a few
-        // values spill, and the wind on 256^3 takes 7.0-8.5 instead of 6.9 ms for four steps)
+        // values spill, and the wind on 256^3 takes 7.0-8.5 instead of 6.7 ms for four steps)
         __syncthreads();
-        top_in();
+        high_in();
         double uin[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[unsigned(tid)];
@@ -1868,7 +1812,7 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     else if (!A.write_dt) dtc = (A.dt + off0)[at];
     const double top = A.want_lam ? running_max(T.lam + sim) : 0.0;
     __syncthreads();
-    top_in();
+    high_in();
     if (POWELL) {
         const double ux = double(sW[1][tid]), uy = double(sW[2][tid]), uz = double(sW[3][tid]);
         const double bx = double(sW[4][tid]), by = double(sW[5][tid]), bz = double(sW[6][tid]);
@@ -1917,8 +1861,8 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     }
 }
 
-// Wavefronts per SIMD the register allocation is sized for. FP64: four (126 VGPRs; the 80 KiB of LDS
-// allow two workgroups per CU anyway). FP32 fluxes: six (80 VGPRs, 60 bytes of spills), so that three
+// Wavefronts per SIMD the register allocation is sized for. FP64: four (124 VGPRs; the 80 KiB of LDS
+// allow two workgroups per CU anyway). FP32 fluxes: six (76 VGPRs), so that three
 // workgroups of 40 KiB share a CU: 24 wavefronts instead of 16, 9 % faster on the 256^3 magnetosphere
 // than four per SIMD at 102 VGPRs; eight per SIMD (64 VGPRs) spills 116 bytes and is 26 % slower.
 template <typename R>
@@ -1927,7 +1871,7 @@ constexpr int blk_waves_per_simd() { return sizeof(R) == 8 ? 4 : 6; }
 template <typename R, int FLUX, bool POWELL, bool VIEW = false>
 __global__ void __launch_bounds__(BLK_NT, (blk_waves_per_simd<R>())) k_stage_blk(Tables T, StageArgs A) {
     using SL = Slab<8>;
-    static_assert(SL::NC - SL::XH >= 8 * 64, "z-flux exchange space");
+    static_assert(SL::NC - SL::ZLO == 768 && SL::ZLO % 2 == 0, "flux exchange space");
     static_assert(sizeof(R) * 2 * 64 >= sizeof(double) * 8 + sizeof(int) * 8, "reduction space");
     __shared__ R sW[8][SL::NC];
     const int wg = blockIdx.x, xcd = wg & 7, slot = wg >> 3;
@@ -2492,7 +2436,7 @@ int32_t launch_stage_prec(const HostGrid &h, const StageArgs &a, int flux, bool 
 
 Shape pick_shape(const bmhd_opts &o) {
     Shape sh;
-    // the block form for every flux and precision (256^3 magnetosphere, HLLE, FP64: 2.2 ms per step against 3.8 for
+    // the block form for every flux and precision (256^3 magnetosphere, HLLE, FP64: 2.05 ms per step against 3.8 for
     // the plane form on 8x8x4 slabs and 4.1 for the face form on full blocks; fast wave on 1,875 blocks with the
     // Linde-type flux: 0.21 against 0.30 ms). A persistent grid or a tile of four layers asks for the plane form.
     // With the face form, full blocks for FP64.
