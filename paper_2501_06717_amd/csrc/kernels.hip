@@ -698,6 +698,45 @@ __device__ __forceinline__ void block_publish(double lam, int nfault, double *re
     }
 }
 
+constexpr int BLK_NT = 512;  // threads of the block form
+
+// block_publish without a barrier, for the block form: each wavefront that has a bound above the running one adds it
+// to the workgroup's in LDS and goes; the last one publishes. tally: wavefronts done (4 bits), those whose cells are
+// all NaN (4 bits), faults. The caller clears top_bits and tally ahead of a barrier. On a loaded device the barrier and
+// the first wavefront's read of the bound kept a workgroup's LDS for 3 of 19 us; without them, and with the high faces'
+// wavefronts first, the 256^3 wind's four steps take 8.56 instead of 8.62 ms (FP32 fluxes: 6.62 instead of 6.69).
+struct WgTally {
+    unsigned long long top_bits;
+    unsigned tally;
+};
+__device__ __forceinline__ void wave_publish(double lam, bool fault, double top, bool all_in_flight, WgTally *g,
+                                             unsigned long long *slot, int32_t *faults) {
+    unsigned add = 1u + (unsigned(__popcll(__ballot(fault))) << 8);
+    if (__ballot(!(lam == 0.0))) {  // else no cell of the wavefront exceeds the running bound
+        const double m = wave_max(lam);
+        if (m != m) add += 16u;
+        else if ((threadIdx.x & 63) == 0) atomicMax(&g->top_bits, (unsigned long long)__double_as_longlong(m));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        const unsigned all = atomicAdd(&g->tally, add) + add;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        if ((all & 15u) == BLK_NT / 64) {
+            const unsigned long long bits = g->top_bits;
+            // bits of a non-negative double order like the double. Where the whole grid is in flight at once (two
+            // workgroups per CU) another look at the bound finds it as it was and only takes time (32^3 cells: 7 us of
+            // 284 over ten steps); on larger ones it spares atomics to one address (32 simulations, 11,000 blocks:
+            // 4.78 ms, 4.85 without)
+            if (slot && bits > (unsigned long long)__double_as_longlong(top)) {
+                if (all_in_flight) atomicMax(slot, bits);
+                else publish_max(slot, __longlong_as_double((long long)bits));
+            }
+            if (slot && ((all >> 4) & 15u) == BLK_NT / 64) atomicMax(slot, 0x7ff8000000000000ull);
+            if (faults && (all >> 8)) atomicAdd(faults, int(all >> 8));
+        }
+    }
+}
+
 __global__ void __launch_bounds__(512) k_dt_reduce(Tables T, const double *__restrict__ U) {
     __shared__ double red[8];
     __shared__ int redi[8];
@@ -1137,7 +1176,7 @@ __device__ __forceinline__ bool learned_rejects(double r, double p, const double
 // Powell source, stage update and write of the thread's own cell (threads below 64 KS own cell tid of
 // the slab), then the end-of-step bookkeeping: positivity check and the next time-step bound. With the
 // learned correction, `rng` (or the LDS primitives when it is null) gives the old neighbourhood range.
-template <int KS, typename R, bool POWELL, bool LEARN, typename Mask, int NT = Slab<KS>::NT>
+template <int KS, typename R, bool POWELL, bool LEARN, typename Mask>
 __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A, int b, int slab, const double (&uin)[8],
                                             R (*sW)[Slab<KS>::NC], Mask sM, double (&rhs)[8], double divb,
                                             double inv_dx, double *red, int *redi, const double *rng = nullptr) {
@@ -1235,8 +1274,8 @@ __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A,
                 if (A.want_lam) lam = cell_bound(w, inv_dx);
             }
         }
-        block_publish<NT>(lam, A.count_faults ? nf : 0, red, redi, A.want_lam ? T.lam + B.sim : nullptr,
-                          A.faults);
+        block_publish<SL::NT>(lam, A.count_faults ? nf : 0, red, redi, A.want_lam ? T.lam + B.sim : nullptr,
+                              A.faults);
     }
 }
 
@@ -1569,7 +1608,10 @@ __global__ void __launch_bounds__(64 * (KS + 1), (wp_waves_per_simd<KS, R>())) k
 // wavefronts to 1,420 and 2.05 ms (1.52 ms; 1,334 instructions). A raised priority for those wavefronts, or other
 // layers for every other block, made no difference.
 
-constexpr int BLK_NT = 512;
+
+// The cell of this thread: wavefronts 0-2 own layers 3-5, so that the wavefronts with one more face pass are the
+// oldest of their SIMDs, which issue first.
+__device__ __forceinline__ int blk_cell() { return (lane_tid() + 3 * 64) & (BLK_NT - 1); }
 
 // Conserved values of the halo cells of face fd of block b that a wavefront gathers, (x, y, z) block-local with
 // one coordinate outside the block: in place from the neighbour's interior, the boundary rule, the halo buffer
@@ -1615,7 +1657,7 @@ __device__ __forceinline__ void gather_blk(const Tables &T, const StageArgs &A, 
                                            R (*sW)[Slab<8>::NC]) {
     using SL = Slab<8>;
     const size_t vs = size_t(T.nb) * 512;
-    const int tid = lane_tid();
+    const int tid = blk_cell();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     double u0[8], u1[8], u2[8];
     const double *own = A.Uin + size_t(b) * 512;
@@ -1679,7 +1721,7 @@ template <typename R, int FLUX, bool POWELL>
 __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A, const DevBlock &B, int b,
                                             R (*sW)[Slab<8>::NC], double inv_dx, bool fc) {
     using SL = Slab<8>;
-    const int tid = lane_tid();
+    const int tid = blk_cell();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = tid & 63, ci = l & 7, cj = l >> 3;
     double rhs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1782,37 +1824,32 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         if (cj == 7) take(576 + w * 8 + ci);
     };
     // the end-of-step reduction, in cells that hold no flux
-    double *red = reinterpret_cast<double *>(&sW[5][SL::ZLO + 640]);
-    int *redi = reinterpret_cast<int *>(&sW[6][SL::ZLO + 640]);
+    WgTally *tally = reinterpret_cast<WgTally *>(&sW[5][SL::ZLO + 640]);
+    if (threadIdx.x == 0) *tally = WgTally{0ull, 0u};
     const size_t vs = size_t(T.nb) * 512, off0 = size_t(b) * 512;
-    if constexpr (sizeof(R) == 4) {
-        // sized for 80 registers: everything is loaded where it is used (with the FP64 form's early loads a few
-        // values spill, and the wind on 256^3 takes 7.0-8.5 instead of 6.7 ms for four steps)
-        __syncthreads();
-        high_in();
-        double uin[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[unsigned(tid)];
-        cell_update<8, R, POWELL, false, BitMask, BLK_NT>(T, A, b, 0, uin, sW, BitMask{nullptr}, rhs, divb, inv_dx, red, redi);
-        return;
-    }
+    // FP32 fluxes are sized for 80 registers: loaded that early, these values would spill
+    constexpr bool EARLY = sizeof(R) == 8;
     const int sim = B.sim, skipm = B.fc_skip;
     // the cell's stage input, U^n, step and the running bound are on their way while the barrier waits. The stage
     // result and U^n are streamed (stored / read once per stage): non-temporal, so that they do not push the
     // neighbours' halo cells out of L2
     const unsigned at = unsigned(tid);
-    double uin[8], u0[8], dtc = 0.0;
+    double uin[8], u0[8], dtc = 0.0, top = 0.0;
+    auto load = [&]() {
 #pragma unroll
-    for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[at];
-    if (A.use_u0) {
+        for (int v = 0; v < 8; ++v) uin[v] = (A.Uin + v * vs + off0)[at];
+        if (EARLY && A.use_u0) {
 #pragma unroll
-        for (int v = 0; v < 8; ++v) u0[v] = __builtin_nontemporal_load(&(A.U0 + v * vs + off0)[at]);
-    }
-    if (!A.local_dt) dtc = A.dt[sim];
-    else if (!A.write_dt) dtc = (A.dt + off0)[at];
-    const double top = A.want_lam ? running_max(T.lam + sim) : 0.0;
+            for (int v = 0; v < 8; ++v) u0[v] = __builtin_nontemporal_load(&(A.U0 + v * vs + off0)[at]);
+        }
+        if (!A.local_dt) dtc = A.dt[sim];
+        else if (!A.write_dt) dtc = (A.dt + off0)[at];
+        top = A.want_lam ? running_max(T.lam + sim) : 0.0;
+    };
+    if constexpr (EARLY) load();
     __syncthreads();
     high_in();
+    if constexpr (!EARLY) load();
     if (POWELL) {
         const double ux = double(sW[1][tid]), uy = double(sW[2][tid]), uz = double(sW[3][tid]);
         const double bx = double(sW[4][tid]), by = double(sW[5][tid]), bz = double(sW[6][tid]);
@@ -1837,7 +1874,10 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     if (A.use_u0) {
         const double a0 = A.alpha, a1 = 1.0 - A.alpha;
 #pragma unroll
-        for (int v = 0; v < 8; ++v) out[v] = a0 * u0[v] + a1 * uin[v] + bdt * rhs[v];
+        for (int v = 0; v < 8; ++v) {
+            const double u = EARLY ? u0[v] : __builtin_nontemporal_load(&(A.U0 + v * vs + off0)[at]);
+            out[v] = a0 * u + a1 * uin[v] + bdt * rhs[v];
+        }
     } else {
 #pragma unroll
         for (int v = 0; v < 8; ++v) out[v] = uin[v] + bdt * rhs[v];
@@ -1849,7 +1889,7 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         const bool later = skipm && (((skipm & 1) && ci == 0) || ((skipm & 2) && ci == 7) || ((skipm & 4) && cj == 0) ||
                                      ((skipm & 8) && cj == 7) || ((skipm & 16) && w == 0) || ((skipm & 32) && w == 7));
         double lam = 0.0;
-        int nf = 0;
+        bool nf = false;
         if (!later) {
             double p[8];
             cons_to_prim(out, p);
@@ -1857,7 +1897,7 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
             // (a cell that is not positive always gives its own bound: the limit holds for positive states)
             if (A.want_lam && (nf || !(bound_limit(p, inv_dx) <= top))) lam = cell_bound(p, inv_dx);
         }
-        block_publish<BLK_NT>(lam, A.count_faults ? nf : 0, red, redi, A.want_lam ? T.lam + sim : nullptr, A.faults);
+        wave_publish(lam, A.count_faults && nf, top, T.nb <= 512, tally, A.want_lam ? T.lam + sim : nullptr, A.faults);
     }
 }
 
