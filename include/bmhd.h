@@ -149,8 +149,8 @@ typedef struct {
                              0 or 8, persist_wgs 0) */
     int32_t persist_wgs;  /* 0: one workgroup per tile; > 0: a persistent grid of this many workgroups
                              (rounded up to a multiple of 8), each looping over tiles */
-    int32_t use_graph;    /* 1: steps after the first replay one captured HIP graph of a whole step
-                             (n_stages must be even; `events` are ignored) */
+    int32_t use_graph;    /* 1: pairs of steps after the first replay one captured HIP graph of two whole
+                             steps (n_stages must be even; `events` are ignored) */
     const bmhd_learned *learned; /* NULL: plain fluxes */
     int32_t n_events;     /* length of `events`, or 0 */
     void **events;        /* optional caller-created hipEvent_t handles: when n_events >= 2 * n_stages,

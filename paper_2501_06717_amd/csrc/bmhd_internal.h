@@ -87,7 +87,7 @@ struct Tables {
     const DevFcCell *fc_cells;
     double *halo;               // [n_halo_slots][HALO_SLOT]
     double *fcbuf;              // [n_fc_rec][FC_REC]
-    unsigned long long *lam;    // [n_sims] max of the dt bound (bit patterns of positive doubles)
+    unsigned long long *lam, *lam_next;  // [n_sims] each: max of the dt bound (bit patterns of positive doubles)
     int32_t nb, ns, n_halo_items, n_fc_cells, n_clear;
 };
 
@@ -112,7 +112,7 @@ struct HostGrid {
     // workspace layout (byte offsets)
     size_t off_blocks = 0, off_sims = 0, off_lut = 0, off_order = 0, off_order_split = 0, off_halo_items = 0,
            off_fc_cells = 0;
-    size_t off_halo = 0, off_fcbuf = 0, off_lam = 0, work_bytes = 0, table_bytes = 0;
+    size_t off_halo = 0, off_fcbuf = 0, off_lam = 0, off_lam_next = 0, work_bytes = 0, table_bytes = 0;
     std::vector<unsigned char> blob;  // packed tables (first table_bytes of the workspace)
     void *d_work = nullptr;
     Tables dev{};

@@ -389,6 +389,7 @@ int32_t build_grid(const bmhd_grid_desc *d, HostGrid &g, std::string &err) {
     g.off_halo_items = off; off = align256(off + sizeof(int32_t) * std::max<size_t>(1, g.halo_items.size()));
     g.off_fc_cells = off; off = align256(off + sizeof(DevFcCell) * std::max<size_t>(1, g.fc_cells.size()));
     g.off_lam = off; off = align256(off + sizeof(unsigned long long) * size_t(g.ns));
+    g.off_lam_next = off; off = align256(off + sizeof(unsigned long long) * size_t(g.ns));
     g.table_bytes = off;
     g.off_halo = off; off = align256(off + sizeof(double) * size_t(HALO_SLOT) * size_t(std::max(1, g.n_halo_slots)));
     g.off_fcbuf = off; off = align256(off + sizeof(double) * size_t(FC_REC) * size_t(std::max(1, g.n_fc_rec)));

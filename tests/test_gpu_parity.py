@@ -369,3 +369,26 @@ def test_autotune_cache(bd, tmp_path, monkeypatch):
     _, ms3 = g.autotune(U0.clone(), U1, dt, n_steps=1, precision="fp32_flux", **kw)
     assert all(v > 0 for v in ms3.values())
     assert len(path.read_text().splitlines()) == 2
+
+
+@pytest.mark.parametrize("n_steps", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("use_graph", [False, True])
+@pytest.mark.parametrize("case", ["batch", "two_level_body"])
+def test_time_step_of_every_step_in_a_call(bd, case, use_graph, n_steps):
+    """dt of each step from the bound that the step before collected, in either of its two places and for
+    every simulation, against dt reduced anew from the state (bmhd_reduce_dt) and one call per step: bit
+    for bit, for pairs of steps replayed from a graph and the steps left over, and again in a second call."""
+    wl = small_batch() if case == "batch" else wk.two_level_magnetosphere(48)
+    kw = dict(flux="hlle", powell=case != "batch")
+    g = bd.Grid.from_workload(wl).upload()
+    A = g.set_state(dev(wl.W)); A1 = torch.zeros_like(A)
+    B = g.set_state(dev(wl.W)); B1 = torch.zeros_like(B)
+    dta = torch.zeros(g.ns, dtype=torch.float64, device="cuda")
+    for rep in range(2):
+        say("dt of every step", case, use_graph, n_steps, rep)
+        g.advance(A, A1, dta, 2 * n_steps, cfl=0.8, use_graph=use_graph, **kw)
+        for _ in range(n_steps):
+            dtb = g.reduce_dt(B, 0.8)
+            g.advance(B, B1, dtb, 2, recompute_dt=False, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(dta, dtb) and torch.equal(A, B) and torch.equal(A1, B1), rep
