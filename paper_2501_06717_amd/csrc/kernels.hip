@@ -2158,34 +2158,34 @@ __global__ void __launch_bounds__(BLK_NT, 4) k_face_data(Tables T, StageArgs A, 
 // Z-scored stencil features of the faces of a block for the learned correction's inference, in the
 // compact face layout (see lrn_y_at), FP32 primitives in LDS (40 KB per block, so several blocks per CU); each
 // thread takes one stencil cell of a face at a time (8 features), so a wavefront's stores cover
-// contiguous memory. TX = __bf16 stores the features rounded as the BF16 network consumes them (half
+// contiguous memory. Bound by memory: 4,096 blocks in 133 us, 4.0 TB/s (146 us with the slabs' general gather in
+// workgroups of nine wavefronts, of which fewer fit on a CU). TX = __bf16 stores the features rounded as the BF16 network consumes them (half
 // the bytes); TX = float keeps them for the FP32 network.
 template <typename TX>
-__global__ void __launch_bounds__(Slab<8>::NT) k_face_features(Tables T, StageArgs A, const float *__restrict__ stats,
-                                                               TX *__restrict__ X) {
+__global__ void __launch_bounds__(BLK_NT, 6) k_face_features(Tables T, StageArgs A, const float *__restrict__ stats,
+                                                             TX *__restrict__ X) {
     using SL = Slab<8>;
     __shared__ float sW[8][SL::NC];
-    __shared__ unsigned char sM[SL::NC];
-    __shared__ float sMean[32], sInv[32];
-    const int b = blockIdx.x;
-    if (threadIdx.x < 32) {
-        sMean[threadIdx.x] = stats[threadIdx.x];
-        sInv[threadIdx.x] = 1.0f / stats[32 + threadIdx.x];
+    const int wg = blockIdx.x, xcd = wg & 7;
+    const int b = T.order[xcd_first(T.nb, xcd) + (wg >> 3)];
+    const DevBlock &B = T.blocks[b];
+    float mean[8], inv[8];  // of this thread's stencil cell
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        mean[v] = stats[(threadIdx.x & 3) * 8 + v];
+        inv[v] = 1.0f / stats[32 + (threadIdx.x & 3) * 8 + v];
     }
-    double u[SL::NPT][8];
-    gather_issue<8>(T, A, b, 0, u);
-    gather_store<8, float>(T, b, 0, u, sW, sM);
+    gather_blk<float, false>(T, A, B, b, sW);
     __syncthreads();
     // task t = 4 f + q: stencil cell q of face f of the compact layout (each face once: the block's low
     // faces, then its high face planes with no neighbour across them), so consecutive lanes write
     // consecutive 32-byte pieces
-    const DevBlock &B = T.blocks[b];
     const int tid = lane_tid();
 #pragma unroll
     for (int D = 0; D < 3; ++D) {
         const bool hb = B.hb_pos[D] >= 0;
         const int ntask = hb ? 4 * (512 + 64) : 4 * 512;
-        for (int t = tid; t < ntask; t += SL::NT) {
+        for (int t = tid; t < ntask; t += BLK_NT) {
             const int f = t >> 2, q = t & 3;
             int p[3];  // face coordinates (x, y, z), the one along D in 0..8
             size_t row;
@@ -2210,7 +2210,7 @@ __global__ void __launch_bounds__(Slab<8>::NT) k_face_features(Tables T, StageAr
                 x[4 + a] = sW[4 + (D + a) % 3][c];
             }
 #pragma unroll
-            for (int v = 0; v < 8; ++v) x[v] = (x[v] - sMean[q * 8 + v]) * sInv[q * 8 + v];
+            for (int v = 0; v < 8; ++v) x[v] = (x[v] - mean[v]) * inv[v];
             TX *dst = X + row * 32 + q * 8;
             if constexpr (std::is_same<TX, __bf16>::value) {
                 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
@@ -2739,13 +2739,13 @@ int32_t enqueue_stage(const HostGrid &h, const bmhd_opts &o, int e, double *d_U0
         const int nrows = h.nb * 1536 + h.n_hb * 64;
         if (L.mode == 0) {  // BF16 network: features stored in BF16 in the first half of x_buf
             uint16_t *xb = reinterpret_cast<uint16_t *>(L.x_buf);
-            k_face_features<__bf16><<<h.nb, Slab<8>::NT, 0, s>>>(h.dev, a, L.stats, reinterpret_cast<__bf16 *>(xb));
+            k_face_features<__bf16><<<h.nb, BLK_NT, 0, s>>>(h.dev, a, L.stats, reinterpret_cast<__bf16 *>(xb));
             if (int32_t rc = launch_check("face features")) return rc;
             std::string err;
             if (int32_t rc = mlp_infer_bf16_inputs(L.params, L.params_bf16, L.hidden, nrows, xb, L.y_buf, s, err))
                 return fail(rc, err);
         } else if (L.mode == 1) {  // FP32 network; mode 2: y_buf is given
-            k_face_features<float><<<h.nb, Slab<8>::NT, 0, s>>>(h.dev, a, L.stats, L.x_buf);
+            k_face_features<float><<<h.nb, BLK_NT, 0, s>>>(h.dev, a, L.stats, L.x_buf);
             if (int32_t rc = launch_check("face features")) return rc;
             if (int32_t rc = bmhd_mlp_forward(L.params, L.params_bf16, L.hidden, nrows, L.x_buf, L.y_buf,
                                               nullptr, L.mode, s))
