@@ -3,17 +3,17 @@
 // Hot path per stage (the GPU solver's block sweep, Algorithm 2, redesigned for MI355X):
 //   k_halo_fill   ghost layers of faces that border another level (restriction / prolongation,
 //                 Sec. 4.2), only on grids with two levels;
-//   k_stage_wp    (default) one workgroup per slab of a block (8 x 8 x KS cells), one wavefront per
-//   / k_stage     cell layer plus one (or, k_stage, one thread per face). It gathers the slab and its
-//                 2-deep face halos from HBM straight into LDS as primitive variables (same-level
-//                 neighbours are read in place: no separate ghost-fill pass), computes every face flux
-//                 once (MC-limited reconstruction, Rusanov or HLLE), hands each flux to the cells on
-//                 both sides (cross-lane permutes and LDS), adds the Powell source (Eqs. 2-4) and
-//                 writes the stage result. The second stage also folds in the next time-step bound
-//                 (wave-level max, one filtered 64-bit atomic per workgroup) and the positivity check;
+//   k_stage_blk   (default) one workgroup per block, or k_stage_wp / k_stage one per slab of a block (8 x 8 x KS
+//                 cells). It gathers the block and its 2-deep face halos from HBM straight into LDS as
+//                 primitive variables (same-level neighbours are read in place: no separate ghost-fill
+//                 pass), computes every face flux once (MC-limited reconstruction; Rusanov, HLLE or
+//                 Linde-type flux), hands each flux to the cells on both sides (cross-lane moves and LDS),
+//                 adds the Powell source (Eqs. 2-4) and writes the stage result. The second stage also folds
+//                 in the next time-step bound and the positivity check, and the first stage of the next step
+//                 forms dt from that bound. k_stage_wp also takes the blocks near a body and the learned form;
 //   k_flux_correct coarse cells next to a coarse-fine face swap their coarse flux for the mean of the
 //                 four fine fluxes (FP64 in every precision form);
-//   k_dt_finalize dt = CFL / max bound per simulation.
+//   k_dt_finalize dt = CFL / max bound per simulation, ahead of a call's first step.
 // Under local time stepping (steady-state sessions, Sec. 5.2) the first stage forms each cell's own CFL
 // step from its FP64 stage input and stores it; the second stage and k_flux_correct read it.
 // Between steps: k_remap moves a state onto an adapted grid (copy, prolongation, restriction).
