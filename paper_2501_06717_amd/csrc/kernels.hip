@@ -756,7 +756,8 @@ __device__ __forceinline__ void block_publish(double lam, int nfault, double *re
 constexpr int BLK_NT = 512;  // threads of the block form
 
 // block_publish without a barrier, for the block form: each wavefront that has a bound above the running one adds it
-// to the workgroup's in LDS and goes; the last one publishes. tally: wavefronts done (4 bits), those whose cells are
+// to the workgroup's in LDS and goes; the last one publishes. A wavefront whose largest bound is not positive (-inf: all
+// its cells of negative density) has none: its bits would exceed every positive double's. tally: wavefronts done (4 bits), those whose cells are
 // all NaN (4 bits), faults. The caller clears top_bits and tally ahead of a barrier. On a loaded device the barrier and
 // the first wavefront's read of the bound kept a workgroup's LDS for 3 of 19 us; without them, and with the high faces'
 // wavefronts first, the 256^3 wind's four steps take 8.56 instead of 8.62 ms (FP32 fluxes: 6.62 instead of 6.69).
@@ -770,7 +771,7 @@ __device__ __forceinline__ void wave_publish(double lam, bool fault, double top,
     if (__ballot(!(lam == 0.0))) {  // else no cell of the wavefront exceeds the running bound
         const double m = wave_max(lam);
         if (m != m) add += 16u;
-        else if ((threadIdx.x & 63) == 0) atomicMax(&g->top_bits, (unsigned long long)__double_as_longlong(m));
+        else if (m > 0.0 && (threadIdx.x & 63) == 0) atomicMax(&g->top_bits, (unsigned long long)__double_as_longlong(m));
     }
     if ((threadIdx.x & 63) == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");

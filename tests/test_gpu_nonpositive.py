@@ -72,3 +72,33 @@ def test_density_and_pressure_near_the_ends_of_the_range(bd, oracle_mod, flux, e
     err = one_stage(bd, oracle_mod, wl, W, dt, flux)
     print("error", err, flush=True)
     assert err <= TOL, err
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_flux"])
+@pytest.mark.parametrize("nroot", [(2, 2, 2), (8, 9, 8)])
+def test_time_step_past_a_layer_of_negative_density(bd, nroot, precision):
+    """A step that leaves two whole cell layers of some blocks at negative density (a thin layer that two streams
+    leave, in one large step): the next step's dt comes from the other cells, as in the reduction of dt from the
+    state, on a grid that is in flight at once and on a larger one."""
+    wl = wk.uniform_state(nroot, W0=(1.0, 0.1, -0.2, 0.0, 0.5, 0.1, 0.1, 0.5))
+    W = wl.W.copy()
+    d = wl.ijk[:, 2, None] * 8 + np.arange(8) - 3
+    W[3] = (np.sign(d) * np.exp(-np.abs(d) / 3.0))[:, :, None, None]
+    W[0][d == 0] = 0.3
+    g = bd.Grid.from_workload(wl).upload()
+    kw = dict(flux="hlle", precision=precision, alpha=(0.0, 0.0), beta=(0.0, 8.0))
+    A = g.set_state(torch.from_numpy(W).cuda()); A1 = torch.zeros_like(A)
+    B = A.clone(); B1 = torch.zeros_like(B)
+    dta = torch.zeros(1, dtype=torch.float64, device="cuda")
+    dtb = torch.zeros_like(dta)
+    print("layer of negative density", nroot, precision, flush=True)
+    g.advance(B, B1, dtb, 2, **kw)
+    first = dtb.item()
+    below = (B[0] <= 0.0).flatten(2).all(2)        # layers, per block
+    assert bool(below.any()) and not bool(below.all())
+    dtb = g.reduce_dt(B, 0.8)
+    g.advance(A, A1, dta, 4, **kw)
+    torch.cuda.synchronize()
+    print("dt", first, dta.item(), dtb.item(), flush=True)
+    assert 0.0 < dtb.item() < float("inf")
+    assert dta.item() == dtb.item()
