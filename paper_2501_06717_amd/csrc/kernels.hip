@@ -217,7 +217,8 @@ __device__ __forceinline__ void flux64(const double wl[8], const double wr[8], c
         const double drho = wr[0] - wl[0], dp = wr[7] - wl[7];
         const double c2 = GAMMA * (wl[7] + wr[7]) * frcp1(wl[0] + wr[0]);
         const double t = drho - dp * frcp1(c2);
-        const double delta = fmax(fmin(fmax(t, drho), 0.0), fmin(t, drho));
+        // minmod(t, drho) as drho clamped to the range between 0 and t: none where t is NaN (no pressure on either side)
+        const double delta = fmax(fmin(fmax(t, 0.0), drho), fmin(t, 0.0));
         const double u0 = 0.5 * (wl[1] + wr[1]), u1 = 0.5 * (wl[2] + wr[2]), u2 = 0.5 * (wl[3] + wr[3]);
         const double lam = fmin(fmax(N == 0 ? u0 : (N == 1 ? u1 : u2), sl), sr);
         const double k = (sl * fmax(lam, 0.0) + sr * fmin(lam, 0.0) - sl * sr) * inv * delta;

@@ -102,3 +102,16 @@ def test_time_step_past_a_layer_of_negative_density(bd, nroot, precision):
     print("dt", first, dta.item(), dtb.item(), flush=True)
     assert 0.0 < dtb.item() < float("inf")
     assert dta.item() == dtb.item()
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_contact_without_pressure(bd, oracle_mod, axis):
+    """A density jump where the pressure is exactly zero on both sides: the Linde-type flux has no sound speed to
+    tell the entropy wave's part of the jump by, and takes none."""
+    wl = wk.uniform_state((2, 2, 2), W0=(1.0, 0.5, -0.25, 0.5, 0.5, 0.25, 0.5, 0.0))
+    W = wl.W.copy()
+    W[0][wl.ijk[:, axis] == 1] = 0.25
+    print("contact without pressure", axis, flush=True)
+    err = one_stage(bd, oracle_mod, wl, W, 0.05, "linde")
+    print("error", err, flush=True)
+    assert err <= TOL, err
