@@ -2790,16 +2790,16 @@ int32_t enqueue_stage(const HostGrid &h, const bmhd_opts &o, int e, double *d_U0
     return BMHD_OK;
 }
 
-// Capture (once per buffer set and options) a graph of two whole steps after the first, an odd and an even one (they
+// Capture (once per workspace, buffer set and options) a graph of two whole steps after the first, an odd and an even one (they
 // swap the places of the dt bound). Kernels only: no memset or copy nodes.
 int32_t ensure_step_graph(HostGrid &h, const bmhd_opts &o, double *d_U0, double *d_U1, double *d_dt,
                           int32_t *d_faults) {
     bmhd_opts ko = o;
     ko.events = nullptr;
     ko.n_events = 0;
-    std::vector<unsigned char> key(sizeof(ko) + 4 * sizeof(void *));
+    std::vector<unsigned char> key(sizeof(ko) + 5 * sizeof(void *));
     std::memcpy(key.data(), &ko, sizeof(ko));
-    void *ptrs[4] = {d_U0, d_U1, d_dt, d_faults};
+    void *ptrs[5] = {d_U0, d_U1, d_dt, d_faults, h.d_work};  // (the kernels hold the tables' addresses)
     std::memcpy(key.data() + sizeof(ko), ptrs, sizeof(ptrs));
     if (h.graph_exec && key == h.graph_key) return BMHD_OK;
     if (h.graph_exec) (void)hipGraphExecDestroy(reinterpret_cast<hipGraphExec_t>(h.graph_exec));

@@ -392,3 +392,26 @@ def test_time_step_of_every_step_in_a_call(bd, case, use_graph, n_steps):
             g.advance(B, B1, dtb, 2, recompute_dt=False, **kw)
         torch.cuda.synchronize()
         assert torch.equal(dta, dtb) and torch.equal(A, B) and torch.equal(A1, B1), rep
+
+
+def test_graph_after_another_upload(bd):
+    """A grid uploaded again has its tables and the bounds between steps in another workspace: steps replayed from a
+    graph then equal the directly launched ones bit for bit, with the old workspace's memory in other use."""
+    wl = small_batch()
+    kw = dict(flux="hlle", powell=True)
+    g = bd.Grid.from_workload(wl).upload()
+    A = g.set_state(dev(wl.W)); A1 = torch.zeros_like(A)
+    B = A.clone(); B1 = torch.zeros_like(B)
+    dta = torch.zeros(g.ns, dtype=torch.float64, device="cuda")
+    dtb = torch.zeros_like(dta)
+    kept = []
+    for rep in range(3):
+        say("graph after upload", rep)
+        g.advance(A, A1, dta, 12, use_graph=True, **kw)
+        g.advance(B, B1, dtb, 12, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(A, B) and torch.equal(A1, B1) and torch.equal(dta, dtb), rep
+        kept.append(g.work)                    # the next upload takes other memory
+        g.upload()
+        assert g.work.data_ptr() != kept[-1].data_ptr()
+        kept[-1].zero_()                       # as another owner of it might
