@@ -2896,8 +2896,10 @@ bool autotune_lookup(const char *path, const std::string &key, int &scheme, int 
     while (fgets(line, sizeof line, f)) {
         char k[600];
         int a = 0, b = 0, c = 0;
-        if (sscanf(line, "%599s %d %d %d", k, &a, &b, &c) == 4 && key == k &&
-            (a == BMHD_SCHEME_FACE || a == BMHD_SCHEME_PLANE) && (b == 4 || b == 8) && (c == 0 || c == 2 || c == 4)) {
+        if (sscanf(line, "%599s %d %d %d", k, &a, &b, &c) != 4 || key != k) continue;
+        const bool slabs = (a == BMHD_SCHEME_FACE || a == BMHD_SCHEME_PLANE) && (b == 4 || b == 8) &&
+                           (c == 0 || c == 2 || c == 4);
+        if (slabs || (a == BMHD_SCHEME_BLOCK && b == 8 && c == 0)) {
             scheme = a;
             slab = b;
             persist = c;

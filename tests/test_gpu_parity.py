@@ -415,3 +415,28 @@ def test_graph_after_another_upload(bd):
         g.upload()
         assert g.work.data_ptr() != kept[-1].data_ptr()
         kept[-1].zero_()                       # as another owner of it might
+
+
+@pytest.mark.parametrize("shape,hit", [((3, 8, 0), True), ((2, 4, 2), True), ((1, 8, 0), True), ((3, 4, 0), False),
+                                       ((3, 8, 2), False), ((4, 8, 0), False)])
+def test_autotune_cache_takes_every_shape_it_writes(bd, tmp_path, monkeypatch, shape, hit):
+    """A cached line of each scheme is returned without timing, whichever shape is the fastest here; one that no tuning
+    writes is not."""
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("BMHD_AUTOTUNE_CACHE", str(path))
+    wl = wk.two_level_box()
+    g = bd.Grid.from_workload(wl).upload()
+    U0 = g.set_state(dev(wl.W))
+    U1 = torch.zeros_like(U0)
+    dt = torch.zeros(1, dtype=torch.float64, device="cuda")
+    kw = dict(flux="hlle", powell=True)
+    g.autotune(U0.clone(), U1, dt, n_steps=1, **kw)
+    key = path.read_text().split()[0]
+    path.write_text(f"{key} {shape[0]} {shape[1]} {shape[2]}\n")
+    best, ms = g.autotune(U0.clone(), U1, dt, n_steps=1, **kw)
+    say("autotune cache", shape, best.scheme, best.slab, best.persist_wgs)
+    assert all((v == -1.0) == hit for v in ms.values())
+    if hit:
+        assert (best.scheme, best.slab) == shape[:2] and (best.persist_wgs > 0) == (shape[2] > 0)
+        g.advance(U0, U1, dt, 2, slab=best.slab, scheme=best.scheme, persist_wgs=best.persist_wgs, **kw)
+        torch.cuda.synchronize()
