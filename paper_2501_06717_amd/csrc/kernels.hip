@@ -1236,9 +1236,6 @@ __device__ __forceinline__ bool learned_rejects(double r, double p, const double
     return bad;
 }
 
-// Powell source, stage update and write of the thread's own cell (threads below 64 KS own cell tid of
-// the slab), then the end-of-step bookkeeping: positivity check and the next time-step bound. With the
-// learned correction, `rng` (or the LDS primitives when it is null) gives the old neighbourhood range.
 // The time step of simulation sim in this stage.
 __device__ __forceinline__ double stage_dt(const StageArgs &A, int sim) {
     return A.lam_in ? A.cfl * (1.0 / __longlong_as_double((long long)A.lam_in[sim])) : A.dt[sim];
@@ -1250,6 +1247,9 @@ __device__ __forceinline__ void hand_on_dt(const StageArgs &A, int sim, double d
     if (A.lam_clear) A.lam_clear[sim] = 0ull;
 }
 
+// Powell source, stage update and write of the thread's own cell (threads below 64 KS own cell tid of
+// the slab), then the end-of-step bookkeeping: positivity check and the next time-step bound. With the
+// learned correction, `rng` (or the LDS primitives when it is null) gives the old neighbourhood range.
 template <int KS, typename R, bool POWELL, bool LEARN, typename Mask>
 __device__ __forceinline__ void cell_update(const Tables &T, const StageArgs &A, int b, int slab, const double (&uin)[8],
                                             R (*sW)[Slab<KS>::NC], Mask sM, double (&rhs)[8], double divb,
@@ -1361,7 +1361,6 @@ __device__ __forceinline__ void slab_compute(const Tables &T, const StageArgs &A
                                              double *red, int *redi) {
     using SL = Slab<KS>;
     const DevBlock &B = T.blocks[b];
-    const DevSim &S = T.sims[B.sim];
     const bool near_body = (B.flags & BF_NEAR_BODY) != 0;
     const int tid = lane_tid();
     const bool owner = tid < SL::NCELLS;
@@ -1502,7 +1501,6 @@ __device__ __forceinline__ void wp_compute(const Tables &T, const StageArgs &A, 
     using SL = Slab<KS>;
     constexpr int NE = 8 * KS;
     const DevBlock &B = T.blocks[b];
-    const DevSim &S = T.sims[B.sim];
     const bool near_body = (B.flags & BF_NEAR_BODY) != 0;
     const BitMask mk{sMb};
     const int tid = lane_tid();
@@ -1791,6 +1789,9 @@ __device__ __forceinline__ double lane_next(double x) {
     const int lo = dpp_next(int(v)), hi = dpp_next(int(v >> 32));
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
+// Where the workgroup's end-of-step bound lies among a variable's cells: past the fluxes.
+constexpr int BLK_TALLY = Slab<8>::ZLO + 640;
+
 // The face passes, the source and the update of one block whose primitives are in LDS.
 template <typename R, int FLUX, bool POWELL>
 __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A, const DevBlock &B, int b,
@@ -1899,7 +1900,7 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         if (cj == 7) take(576 + w * 8 + ci);
     };
     // the end-of-step reduction, in cells that hold no flux
-    WgTally *tally = reinterpret_cast<WgTally *>(&sW[5][SL::ZLO + 640]);
+    WgTally *tally = reinterpret_cast<WgTally *>(&sW[5][BLK_TALLY]);
     if (threadIdx.x == 0) *tally = WgTally{0ull, 0u};
     const size_t vs = size_t(T.nb) * 512, off0 = size_t(b) * 512;
     // FP32 fluxes are sized for 80 registers: loaded that early, these values would spill
@@ -1988,8 +1989,9 @@ template <typename R, int FLUX, bool POWELL, bool VIEW = false>
 __global__ void __launch_bounds__(BLK_NT, (blk_waves_per_simd<R>())) k_stage_blk(Tables T, StageArgs A) {
     using SL = Slab<8>;
     static_assert(SL::NC - SL::ZLO == 768 && SL::ZLO % 2 == 0, "flux exchange space");
-    static_assert(sizeof(R) * 2 * 64 >= sizeof(double) * 8 + sizeof(int) * 8, "reduction space");
-    __shared__ R sW[8][SL::NC];
+    static_assert(sizeof(WgTally) <= 128 * sizeof(R) && (5 * SL::NC + BLK_TALLY) * sizeof(R) % alignof(WgTally) == 0,
+                  "reduction space: the cells of variable 5 past the fluxes (the normal fields take those of 0-4)");
+    __shared__ __attribute__((aligned(16))) R sW[8][SL::NC];
     const int wg = blockIdx.x, xcd = wg & 7, slot = wg >> 3;
     const int b = sched_block(T, A, xcd_first(sched_count(T, A), xcd) + slot);
     const DevBlock &B = T.blocks[b];
