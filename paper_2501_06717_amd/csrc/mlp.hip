@@ -865,8 +865,9 @@ int32_t backward_impl(const float *d_params, int32_t hidden, int32_t n, const fl
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int H = hidden;
     const MlpView V = mlp_view(H);
-    // BF16 products: the fused pass, unless the work area cannot hold its layout (its padding to 32 samples: up to
-    // 89 samples) or is not aligned for it; the products below also are the FP32 reference mode
+    // BF16 products: the fused pass, unless the work area cannot hold its layout (padded to 32 samples, which it has no
+    // room for at some sizes up to 65, 72 and 101 samples for H = 32, 64 and 128) or is not aligned for it; the
+    // products below also are the FP32 reference mode
     const BackLayout lay = back_layout(H, n, bmhd_mlp_work_bytes(hidden, n) / sizeof(float));
     if (mode == 0 && lay.splits && (reinterpret_cast<uintptr_t>(d_work) & 15u) == 0) {
         if (H == 32) return backward_fused<32>(lay, d_params, n, d_x, d_t, d_save, d_y, d_grad, d_sqerr, d_work, s);

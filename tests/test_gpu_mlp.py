@@ -131,3 +131,10 @@ def test_bf16_gradients_against_their_rounding_points(bd, H, n):
         if l > 0:
             s = torch.sigmoid(z[l - 1])
             d = (_bf16(d) @ _bf16(w)).float() * (s * (1.0 + z[l - 1] * (1.0 - s)))
+
+
+@pytest.mark.parametrize("H,n", [(32, 64), (32, 65), (32, 66), (64, 32), (64, 33), (64, 72), (64, 73), (128, 76), (128, 77),
+                                 (128, 96), (128, 97), (128, 101), (128, 102)])
+def test_bf16_gradients_where_the_work_area_starts_to_hold_the_fused_layout(bd, H, n):
+    """Both sides of each size at which the backward pass changes between its two forms."""
+    test_bf16_gradients_against_their_rounding_points(bd, H, n)
