@@ -27,6 +27,9 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <memory>
+#include <new>
+#include <stdexcept>
 #include <string>
 #include <vector>
 
@@ -505,17 +508,28 @@ ViewStage view_stage(const bmhd_xchg *x, int r, const double *d_view) {
 namespace bmhd {
 namespace {
 int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bool stage_mode, bmhd_xchg **out);
+
+// The host tables' vectors must not throw through a C entry.
+template <typename F>
+int32_t no_throw(F f) {
+    try {
+        return f();
+    } catch (const std::bad_alloc &) {
+    } catch (const std::length_error &) {
+    }
+    return set_last_error(BMHD_ENOMEM, "out of memory");
+}
 }  // namespace
 }  // namespace bmhd
 
 extern "C" {
 
 int32_t bmhd_xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bmhd_xchg **out) {
-    return xchg_create(g, rank, n_ranks, false, out);
+    return no_throw([&] { return xchg_create(g, rank, n_ranks, false, out); });
 }
 
 int32_t bmhd_xchg_create_for_stage(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bmhd_xchg **out) {
-    return xchg_create(g, rank, n_ranks, true, out);
+    return no_throw([&] { return xchg_create(g, rank, n_ranks, true, out); });
 }
 
 }  // extern "C"
@@ -527,7 +541,8 @@ int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bo
     const HostGrid &h = g->h;
     for (int b = 0; b < h.nb; ++b)
         if (rank[b] < 0 || rank[b] >= n_ranks) return set_last_error(BMHD_EINVAL, "xchg_create: rank out of range");
-    bmhd_xchg *x = new bmhd_xchg;
+    std::unique_ptr<bmhd_xchg> owned(new bmhd_xchg);
+    bmhd_xchg *x = owned.get();
     x->grid = g;
     x->stage_mode = stage_mode;
     x->nr = n_ranks;
@@ -759,38 +774,11 @@ int32_t xchg_create(const bmhd_grid *g, const int32_t *rank, int32_t n_ranks, bo
     x->off_vat = off;
     off = align256(off + 2 * sizeof(int64_t) * std::max<size_t>(1, x->rank.size()));
     x->work_bytes = off;
-    *out = x;
-    return BMHD_OK;
-}
-}  // namespace
-}  // namespace bmhd
-
-extern "C" {
-
-void bmhd_xchg_destroy(bmhd_xchg *x) { delete x; }
-
-int32_t bmhd_xchg_sizes(const bmhd_xchg *x, int32_t *h_nloc, int64_t *h_len, size_t *work_bytes) {
-    if (!x) return set_last_error(BMHD_EINVAL, "null exchange");
-    const int nr = x->nr;
-    if (h_nloc)
-        for (int r = 0; r < nr; ++r) h_nloc[r] = x->nloc[r];
-    if (h_len)
-        for (int p = 0; p < 2; ++p)
-            for (size_t q = 0; q < size_t(nr) * nr; ++q) h_len[size_t(p) * nr * nr + q] = x->len[p][q];
-    if (work_bytes) *work_bytes = x->work_bytes;
+    *out = owned.release();
     return BMHD_OK;
 }
 
-int64_t bmhd_xchg_messages(const bmhd_xchg *x, int64_t *h_out, int64_t max_rows) {
-    if (!x) return set_last_error(BMHD_EINVAL, "null exchange");
-    const int64_t n = int64_t(x->table.size());
-    if (!h_out) return n;
-    if (max_rows < n) return set_last_error(BMHD_ENOMEM, "xchg_messages: output too small");
-    for (int64_t q = 0; q < n; ++q) std::memcpy(h_out + q * 16, x->table[size_t(q)].data(), 16 * sizeof(int64_t));
-    return n;
-}
-
-int32_t bmhd_xchg_upload(bmhd_xchg *x, void *d_work, size_t work_bytes, void *stream) {
+int32_t xchg_upload(bmhd_xchg *x, void *d_work, size_t work_bytes, void *stream) {
     if (!x || !d_work || (reinterpret_cast<uintptr_t>(d_work) & 255u))
         return set_last_error(BMHD_EINVAL, "xchg_upload: null or misaligned workspace");
     if (work_bytes < x->work_bytes) return set_last_error(BMHD_ENOMEM, "xchg_upload: workspace too small");
@@ -832,6 +820,37 @@ int32_t bmhd_xchg_upload(bmhd_xchg *x, void *d_work, size_t work_bytes, void *st
     if (int32_t rc = hip_ok(hipStreamSynchronize(s), "xchg upload sync")) return rc;
     x->d_work = d_work;
     return BMHD_OK;
+}
+}  // namespace
+}  // namespace bmhd
+
+extern "C" {
+
+void bmhd_xchg_destroy(bmhd_xchg *x) { delete x; }
+
+int32_t bmhd_xchg_sizes(const bmhd_xchg *x, int32_t *h_nloc, int64_t *h_len, size_t *work_bytes) {
+    if (!x) return set_last_error(BMHD_EINVAL, "null exchange");
+    const int nr = x->nr;
+    if (h_nloc)
+        for (int r = 0; r < nr; ++r) h_nloc[r] = x->nloc[r];
+    if (h_len)
+        for (int p = 0; p < 2; ++p)
+            for (size_t q = 0; q < size_t(nr) * nr; ++q) h_len[size_t(p) * nr * nr + q] = x->len[p][q];
+    if (work_bytes) *work_bytes = x->work_bytes;
+    return BMHD_OK;
+}
+
+int64_t bmhd_xchg_messages(const bmhd_xchg *x, int64_t *h_out, int64_t max_rows) {
+    if (!x) return set_last_error(BMHD_EINVAL, "null exchange");
+    const int64_t n = int64_t(x->table.size());
+    if (!h_out) return n;
+    if (max_rows < n) return set_last_error(BMHD_ENOMEM, "xchg_messages: output too small");
+    for (int64_t q = 0; q < n; ++q) std::memcpy(h_out + q * 16, x->table[size_t(q)].data(), 16 * sizeof(int64_t));
+    return n;
+}
+
+int32_t bmhd_xchg_upload(bmhd_xchg *x, void *d_work, size_t work_bytes, void *stream) {
+    return no_throw([&] { return xchg_upload(x, d_work, work_bytes, stream); });
 }
 
 int32_t bmhd_xchg_interior(const bmhd_xchg *x, int32_t r, const double *d_U, double *d_view, void *stream) {

@@ -2,11 +2,17 @@
 counts the same message maps as the oracle (integer-equal rows: sender, receiver, pass, index, start
 offset with the n_C = 7 header, blocks, slot, type, receive box) for every grid shape and assignment of
 blocks to processes, and its buffer sizes are the counted ones."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
 from paper_2501_06717_amd import binding as bd
 from paper_2501_06717_amd import workloads as wk
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 GRIDS = {
     "periodic_2x2x2": lambda: wk.uniform_state((2, 2, 2)),
@@ -83,3 +89,27 @@ def test_rank_list_must_cover_every_block():
         bd.Xchg(g, np.zeros(1, np.int32), 1)
     with pytest.raises(bd.BmhdError):
         bd.Xchg(g, np.array([0, 2], np.int32), 2)
+
+
+NO_MEMORY = """
+import resource
+import numpy as np
+from paper_2501_06717_amd import binding as bd, workloads as wk
+wl = wk.uniform_state((2, 2, 2))
+g = bd.Grid.from_workload(wl)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + 2 ** 30, resource.getrlimit(resource.RLIMIT_AS)[1]))
+for for_stage in (False, True):
+    try:
+        bd.Xchg(g, np.zeros(wl.n_blocks, np.int32), 200000, for_stage=for_stage)
+    except bd.BmhdError as e:
+        print("refused:", e)
+"""
+
+
+def test_out_of_host_memory_is_an_error():
+    """Tables of every pair of processes that do not fit the address space (320 GB under a limit of 1 GB): the call
+    returns its error, it does not end the program."""
+    r = subprocess.run([sys.executable, "-c", NO_MEMORY], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.count("refused: bmhd error -3") == 2, r.stdout
