@@ -138,3 +138,18 @@ def test_bf16_gradients_against_their_rounding_points(bd, H, n):
 def test_bf16_gradients_where_the_work_area_starts_to_hold_the_fused_layout(bd, H, n):
     """Both sides of each size at which the backward pass changes between its two forms."""
     test_bf16_gradients_against_their_rounding_points(bd, H, n)
+
+
+@pytest.mark.parametrize("H,n", [(32, 98304), (32, 98305), (64, 294912), (64, 294913), (128, 294912), (128, 294913)])
+def test_saving_forward_where_it_changes_form(bd, H, n):
+    """Both sides of the batch size at which the forward that saves its pre-activations changes form: outputs equal the
+    inference kernel's, and outputs and pre-activations those of a small batch of the same samples, bit for bit."""
+    torch.manual_seed(H)
+    net = bd.Mlp(H, 0.2 * torch.randn(int(bd.lib().bmhd_mlp_n_params(H))))
+    x = torch.randn(n, 32, device="cuda")
+    print("saving forward", H, n, flush=True)
+    y, z = net.forward(x, save=True)
+    assert torch.equal(y, net.forward(x))
+    for rows in (slice(0, 1000), slice(n - 1001, n)):
+        ys, zs = net.forward(x[rows].contiguous(), save=True)
+        assert torch.equal(y[rows], ys) and torch.equal(z[:, rows], zs)
