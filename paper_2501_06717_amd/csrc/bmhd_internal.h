@@ -4,6 +4,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -109,6 +110,8 @@ struct HostGrid {
     std::vector<int32_t> halo_items;
     std::vector<DevFcCell> fc_cells;
     int32_t n_halo_slots = 0, n_fc_rec = 0;
+    mutable std::vector<int32_t> nbr;  // [nb][26][5], formed by the first call that asks for it
+    mutable std::once_flag nbr_once;
     // workspace layout (byte offsets)
     size_t off_blocks = 0, off_sims = 0, off_lut = 0, off_order = 0, off_order_split = 0, off_halo_items = 0,
            off_fc_cells = 0;

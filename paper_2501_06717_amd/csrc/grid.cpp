@@ -69,8 +69,8 @@ void prim_to_cons_host(const double *w, double *u) {
     u[7] = w[7] / (5.0 / 3.0 - 1.0) + 0.5 * rho * u2 + 0.5 * b2;
 }
 
-// The 26-direction neighbour table reported through the ABI; formed when it is asked for (nothing else reads it, and
-// it is half of the work of a grid).
+// The 26-direction neighbour table reported through the ABI; formed when it is first asked for (nothing else reads it,
+// and it is half of the work of a grid).
 void neighbor_table(const HostGrid &g, int32_t *out) {
     Lookup L{&g};
     std::fill(out, out + size_t(g.nb) * NDIR * 5, -1);

@@ -2973,7 +2973,17 @@ int32_t bmhd_grid_info_get(const bmhd_grid *g, bmhd_grid_info *info) {
 
 int32_t bmhd_grid_neighbors(const bmhd_grid *g, int32_t *h_out) {
     if (!g || !h_out) return fail(BMHD_EINVAL, "null argument");
-    neighbor_table(g->h, h_out);
+    const HostGrid &h = g->h;
+    try {
+        std::call_once(h.nbr_once, [&h] {
+            std::vector<int32_t> t(size_t(h.nb) * NDIR * 5);
+            neighbor_table(h, t.data());
+            h.nbr.swap(t);
+        });
+    } catch (const std::bad_alloc &) {
+        return fail(BMHD_ENOMEM, "out of memory");
+    }
+    std::memcpy(h_out, h.nbr.data(), sizeof(int32_t) * h.nbr.size());
     return BMHD_OK;
 }
 
