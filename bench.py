@@ -33,7 +33,7 @@ HBM_PEAK_GBS = 8000.0
 # FETCH_SIZE and WRITE_SIZE runs scaled by a plain device copy (the summaries under profiles/); valid
 # only for the kernel version they were taken on, keyed by (scheme, tile depth)
 TRAFFIC = {
-    ("block", 8): (2.229e9 + 1.074e9, 3.331e9 + 1.074e9),
+    ("block", 8): (2.266e9 + 1.074e9, 3.371e9 + 1.074e9),
 }
 
 
@@ -41,7 +41,7 @@ TRAFFIC = {
 # stages, SQ_INSTS_VALU x 64 / cells from a rocprofv3 counter run; the summary under profiles/), keyed
 # like TRAFFIC; the VALU issue peak is one wave64 instruction per CU per clock (4 SIMDs x 16 lanes):
 # 256 CUs x 2.4 GHz x 64 lanes
-VALU_PER_CELL_STAGE = {("block", 8): 1407.0}
+VALU_PER_CELL_STAGE = {("block", 8): 1414.0}
 VALU_PEAK_LANE_OPS = 256 * 2.4e9 * 64
 
 
@@ -362,8 +362,9 @@ def bench_exchange(reps=20):
     log(f"exchange: pack {tp * 1e6:.1f} us ({sent / 1e6:.1f} MB), unpack {tu * 1e6:.1f} us ({recv / 1e6:.1f} MB)")
     del views, sends, recvs
     # whole steps with the eight processes advanced separately from their exchanged views (every process's
-    # exchange and stage run one after another on this one GPU), beside the single-process step on the
-    # same grid with the same per-step dt; the first step of each warms up
+    # part of a kernel in one launch on this one GPU, bmhd_xchg_all and bmhd_xchg_stage_all; not what a process on
+    # a GPU of its own would run), beside the single-process step on the same grid with the same per-step dt;
+    # the first step of each warms up
     steps = 3
     walls = {}
     x = binding.Xchg(g, rank, 8, for_stage=True).upload()
@@ -386,7 +387,7 @@ def bench_exchange(reps=20):
     out["single_step_ms"] = walls["single"] * 1e3
     out["sharded_note"] = ("stage-mode maps: each process's stage reads the ghost cells of faces whose neighbour is "
                            "on another process from its view and the rest in place; the exchange copies only the "
-                           "sending blocks' interiors; on one GPU the eight processes run one after another")
+                           "sending blocks' interiors; on one GPU the eight virtual processes share one launch per kernel")
     log(f"exchange: sharded step {walls['sharded'] * 1e3:.2f} ms, single-process step {walls['single'] * 1e3:.2f} ms")
     del x, g
     torch.cuda.synchronize()

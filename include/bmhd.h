@@ -12,8 +12,9 @@
  *   - Every device pointer is memory the caller owns (PyTorch tensors in the Python binding). The
  *     library never allocates device memory. Pointers must be 8-byte aligned; d_work 256-byte aligned.
  *   - `stream` is a hipStream_t passed as void*; NULL means the default stream. Every call that takes
- *     a stream only enqueues work on it and returns; nothing is synchronised. bmhd_advance may run part
- *     of a stage (the blocks near a body) on a side stream that the grid owns, made to wait for
+ *     a stream only enqueues work on it and returns; nothing is synchronised. bmhd_advance and
+ *     bmhd_xchg_stage_all may run part of a stage (the blocks near a body, in bmhd_advance also those at a
+ *     level change) on a side stream that the grid owns, made to wait for
  *     `stream` by an event and joined back into `stream` by another before the call returns, so all of
  *     its work is ordered on `stream` as if it ran there (while `stream` is being captured into a
  *     graph, everything stays on `stream`).
@@ -395,7 +396,8 @@ int32_t bmhd_xchg_stage(const bmhd_xchg *x, int32_t r, int32_t stage, const doub
 int32_t bmhd_xchg_flux_correct(const bmhd_xchg *x, int32_t r, int32_t stage, double *d_Uout, const double *d_dt,
                                const bmhd_opts *o, int32_t *d_faults, void *stream);
 
-/* Every process's part at once (the processes of one GPU): bmhd_xchg_interior, then both passes' packs, transfers and
+/* Every process's part at once, for the virtual processes of one GPU (a process on a GPU of its own makes the calls
+ * above, which these leave as they are): bmhd_xchg_interior, then both passes' packs, transfers and
  * unpacks (Sec. 4.4), one launch per kernel instead of one per process, the packs writing straight into the
  * receivers' buffers. d_views holds the views one after another in process order (process r's starts at
  * 8 * 1728 * (blocks of the processes before it) doubles), d_buf all receive buffers of a pass one after another (at least
@@ -404,7 +406,8 @@ int32_t bmhd_xchg_flux_correct(const bmhd_xchg *x, int32_t r, int32_t stage, dou
 int32_t bmhd_xchg_all(const bmhd_xchg *x, const double *d_U, double *d_views, double *d_buf, int32_t *d_bad,
                       void *stream);
 /* bmhd_xchg_stage for every process, then bmhd_xchg_flux_correct for every process: one stage of the whole grid from
- * the views of bmhd_xchg_all. The same results bit for bit. */
+ * the views of bmhd_xchg_all. The same results bit for bit. As in bmhd_advance, the blocks near a body run on the
+ * grid's side stream (on `stream` while that is being captured), so no other call on the grid may run beside it. */
 int32_t bmhd_xchg_stage_all(const bmhd_xchg *x, int32_t stage, const double *d_views, const double *d_U0,
                             const double *d_Uin, double *d_Uout, const double *d_dt, const bmhd_opts *o,
                             int32_t *d_faults, void *stream);

@@ -299,9 +299,9 @@ __device__ __forceinline__ void num_flux(const R wl[8], const R wr[8], R f[8]) {
 }
 
 // Half of the monotonized-central limited slope, minmod(2 dm, (dm + dp) / 2, 2 dp) / 2, from the two
-// one-sided differences: (dm + dp) / 4 clamped to the range between 0 and minmod(dm, dp). Every form below
-// gives the same value bit for bit (scalings by powers of two, comparisons). FP32: two v_med3; FP64 has no
-// median instruction, and six min / max cost less than the sign products (v_mul_f64 twice, a copied sign and
+// one-sided differences: (dm + dp) / 4 clamped to the range between 0 and minmod(dm, dp). For finite differences
+// every form below gives the same value bit for bit (scalings by powers of two, comparisons). FP32: two v_med3; FP64
+// has no median instruction, and six min / max cost less than the sign products (v_mul_f64 twice, a copied sign and
 // its constant, two min, max, the product with the sign).
 __device__ __forceinline__ double mc_half(double dm, double dp) {
     double quarter = 0.25;
@@ -761,7 +761,7 @@ constexpr int BLK_NT = 512;  // threads of the block form
 // its cells of negative density) has none: its bits would exceed every positive double's. tally: wavefronts done (4 bits), those whose cells are
 // all NaN (4 bits), faults. The caller clears top_bits and tally ahead of a barrier. On a loaded device the barrier and
 // the first wavefront's read of the bound kept a workgroup's LDS for 3 of 19 us; without them, and with the high faces'
-// wavefronts first, the 256^3 wind's four steps take 8.56 instead of 8.62 ms (FP32 fluxes: 6.62 instead of 6.69).
+// wavefronts first, the 256^3 wind's four steps take 8.47 instead of 8.51 ms (FP32 fluxes: 6.54 instead of 6.61).
 struct WgTally {
     unsigned long long top_bits;
     unsigned tally;
@@ -1678,7 +1678,7 @@ __global__ void __launch_bounds__(64 * (KS + 1), (wp_waves_per_simd<KS, R>())) k
 // wavefront (one face's halo per load), LDS indices by selects instead of the general slab numbering's
 // branches, the flux of num_flux64 and the limiter of mc_half took it from 2,126 to 1,718 instructions per
 // wavefront and the 256^3 wind's step from 2.55 to 2.2 ms (FP32 fluxes: 1.78 to 1.58 ms), the high faces' own
-// wavefronts to 1,420 and 2.05 ms (1.52 ms; 1,334 instructions). A raised priority for those wavefronts, or other
+// wavefronts to 1,414 and 2.05 ms (1.52 ms; 1,286 instructions). A raised priority for those wavefronts, or other
 // layers for every other block, made no difference.
 
 
@@ -1978,8 +1978,8 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     }
 }
 
-// Wavefronts per SIMD the register allocation is sized for. FP64: four (124 VGPRs; the 80 KiB of LDS
-// allow two workgroups per CU anyway). FP32 fluxes: six (76 VGPRs), so that three
+// Wavefronts per SIMD the register allocation is sized for. FP64: four (101-120 VGPRs; the 80 KiB of LDS
+// allow two workgroups per CU anyway). FP32 fluxes: six (70-80 VGPRs), so that three
 // workgroups of 40 KiB share a CU: 24 wavefronts instead of 16, 9 % faster on the 256^3 magnetosphere
 // than four per SIMD at 102 VGPRs; eight per SIMD (64 VGPRs) spills 116 bytes and is 26 % slower.
 template <typename R>
