@@ -1811,21 +1811,26 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
         blk_face<R, 0, FLUX>(sW, c, f, bb);
         if (fc) record_fc<0>(T, B, ci, cj, w, f);
     }
-    // the next lane's flux enters with weight inv_dx, or 0 in the last column (its high face comes later)
-    const double wx = ci < 7 ? inv_dx : 0.0, wy = cj < 7 ? inv_dx : 0.0;
-#pragma unroll
-    for (int v = 0; v < 8; ++v) {
-        const R g = lane_next(f[v]);
-        rhs[v] = fma(double(f[v]), inv_dx, rhs[v]);
-        rhs[v] = fma(-double(g), wx, rhs[v]);
-    }
+    // the next lane's flux enters too, but not in the last column (its high face comes later): left out there, not
+    // weighted by 0, for it is the flux of another row's first face and need not be finite
     {
-        const R g = lane_next(bb);
+        R g[9];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) g[v] = lane_next(f[v]);
+        g[8] = lane_next(bb);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) rhs[v] = fma(double(f[v]), inv_dx, rhs[v]);
         divb = fma(-double(bb), inv_dx, divb);
-        divb = fma(double(g), wx, divb);
+        if (ci < 7) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) rhs[v] = fma(-double(g[v]), inv_dx, rhs[v]);
+            divb = fma(double(g[8]), inv_dx, divb);
+        }
     }
 
-    // y: the low-y face of each cell; the cell below is eight lanes on
+    // y: the low-y face of each cell; the cell below is eight lanes on (in the last row the lane's own flux comes back, to
+    // enter with weight 0)
+    const double wy = cj < 7 ? inv_dx : 0.0;
     {
         const int h = SL::YH + w * 32 + ci;
         const int c[4] = {cj < 2 ? h + cj * 8 : tid - 16, cj < 1 ? h + 8 : tid - 8, tid, cj > 6 ? h + 16 : tid + 8};

@@ -115,3 +115,32 @@ def test_contact_without_pressure(bd, oracle_mod, axis):
     err = one_stage(bd, oracle_mod, wl, W, 0.05, "linde")
     print("error", err, flush=True)
     assert err <= TOL, err
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_flux"])
+@pytest.mark.parametrize("flux", ["rusanov", "hlle", "linde"])
+def test_flux_that_is_not_finite_stays_with_its_cells(bd, oracle_mod, flux, precision):
+    """Negative density on both sides of a block's first x face in one row: that flux has no real value, and only the
+    two cells it belongs to are lost, no cell of another row."""
+    wl = wk.uniform_state((3, 1, 1))
+    W = wl.W.copy()
+    for j, k in ((1, 0), (2, 3), (5, 4), (7, 7)):
+        for b, i in ((0, 7), (1, 0)):
+            W[0, b, k, j, i] = -0.01
+    print("flux that is not finite", flux, precision, flush=True)
+    g = bd.Grid.from_workload(wl).upload()
+    U0 = g.set_state(torch.from_numpy(W).cuda())
+    U1 = torch.zeros_like(U0)
+    dt = torch.full((1,), 0.05, dtype=torch.float64, device="cuda")
+    g.advance(U0, U1, dt, 1, flux=flux, precision=precision, recompute_dt=False)
+    torch.cuda.synchronize()
+    o = oracle_mod.Grid.from_workload(wl)
+    R0 = o.set_state(W)
+    R1 = np.zeros_like(R0)
+    o.advance(R0, R1, [0.05], 1, flux=flux, recompute_dt=False)
+    fin = np.isfinite(R1)
+    assert (~fin[0]).sum() == 8                # four faces, two cells each
+    got = U1.cpu().numpy()
+    assert np.array_equal(np.isfinite(got), fin)
+    if precision == "fp64":
+        assert np.abs(got[fin] - R1[fin]).max() <= TOL * np.abs(R1[fin]).max()
