@@ -1983,7 +1983,7 @@ __device__ __forceinline__ void blk_compute(const Tables &T, const StageArgs &A,
     }
 }
 
-// Wavefronts per SIMD the register allocation is sized for. FP64: four (101-120 VGPRs; the 80 KiB of LDS
+// Wavefronts per SIMD the register allocation is sized for. FP64: four (88-104 VGPRs; the 80 KiB of LDS
 // allow two workgroups per CU anyway). FP32 fluxes: six (70-80 VGPRs), so that three
 // workgroups of 40 KiB share a CU: 24 wavefronts instead of 16, 9 % faster on the 256^3 magnetosphere
 // than four per SIMD at 102 VGPRs; eight per SIMD (64 VGPRs) spills 116 bytes and is 26 % slower.
